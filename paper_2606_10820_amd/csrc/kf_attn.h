@@ -132,10 +132,26 @@ __device__ __forceinline__ void attention_tiles(const bf16* __restrict__ Q, cons
   };
   auto tile = [&](int t0, const Frag& f) {
     bf16x8_t v[NDB];
+    if constexpr (DH == 32) {
+      // d_head 32 zeroes the slots past the end with dword masks, on every
+      // tile: from the branch below the compiler gave the value fragment and
+      // the probabilities of this width overlapping registers (wrong outputs
+      // from the second tile of a wavefront on).
+      const int left = nkeys - (t0 + 8 * gq);
+      uint32_t keep[4];
 #pragma unroll
-    for (int db = 0; db < NDB; ++db)
-      v[db] = __builtin_bit_cast(bf16x8_t, u32x4_t{f.vlo[db].x, f.vlo[db].y, f.vhi[db].x, f.vhi[db].y});
-    if (t0 + KT > nkeys) {  // the ragged last tile: zero the value slots past the end
+      for (int i = 0; i < 4; ++i)
+        keep[i] = (2 * i < left ? 0xffffu : 0u) | (2 * i + 1 < left ? 0xffff0000u : 0u);
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+        v[db] = __builtin_bit_cast(bf16x8_t, u32x4_t{f.vlo[db].x & keep[0], f.vlo[db].y & keep[1],
+                                                     f.vhi[db].x & keep[2], f.vhi[db].y & keep[3]});
+    } else {
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+        v[db] = __builtin_bit_cast(bf16x8_t, u32x4_t{f.vlo[db].x, f.vlo[db].y, f.vhi[db].x, f.vhi[db].y});
+    }
+    if (DH != 32 && t0 + KT > nkeys) {  // the ragged last tile: zero the value slots past the end
       const int kb = t0 + 8 * gq;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
