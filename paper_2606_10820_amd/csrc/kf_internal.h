@@ -409,4 +409,10 @@ hipError_t launch_training_attention_seq(int mask, int B, int H, int N, int k, i
                                          const bf16* K, const bf16* V, int ldk, bf16* O,
                                          float scale, hipStream_t s);
 
+// Attention of a step with many query rows per sequence over the KV cache
+// (bf16, g.qoff = 0): the result of launch_attention, tiles shared by 128 rows.
+hipError_t launch_prefill_attention(const bf16* Q, const bf16* kv, bf16* O, const KfDevState* st,
+                                    const KfStepGeom& g, const KfKvGeom& kg, int layer,
+                                    float scale, hipStream_t s);
+
 }  // namespace kf

@@ -735,6 +735,12 @@ hipError_t launch_noise_sinusoid(T* S, const float* noise, uint64_t seed, const 
 // keep four wavefronts (batch 24 and 32 lost 5 %, batch 64 9 %, batch 256
 // 15 % with eight).
 constexpr int kWideMin = 64;
+// Steps of at least this many rows per sequence (prefills, admissions) run the
+// kernel whose tiles serve 128 query rows.  Measured per layer, decode kernel
+// against it: R = 32 at d_head 64, B = 1 10 us (two kernels) against 6, B = 64
+// 8 against 6; R = 20 lies within the noise of itself.  Grids that the
+// eight-wavefront decode kernel takes keep it (B = 1, R = 256: 9 us against 10).
+constexpr int kPrefillRows = 32;
 
 template <typename T>
 hipError_t launch_attention(const T* Q, const T* kv, T* O, const KfDevState* st, KfStepGeom g,
@@ -753,6 +759,9 @@ hipError_t launch_attention(const T* Q, const T* kv, T* O, const KfDevState* st,
       while (ns > 1 && (long long)g.B * kg.H * g.R * ns > ws.entries) --ns;
       if (ns < 1) ns = 1;
     }
+    const bool wide = kg.dh == 64 && ns > 1 && base >= kWideMin;
+    if (g.qoff == 0 && g.R >= kPrefillRows && !wide)
+      return launch_prefill_attention(Q, kv, O, st, g, kg, layer, scale, s);
     AttnSplit sp = ws;
     sp.ns = ns;
     dim3 grid(base * ns);
@@ -764,7 +773,7 @@ hipError_t launch_attention(const T* Q, const T* kv, T* O, const KfDevState* st,
                              O, g, kg.H, sp);
         break;
       case 64:
-        if (ns > 1 && base >= kWideMin) {  // eight wavefronts, no key split
+        if (wide) {  // eight wavefronts, no key split
           sp.ns = 1;
           launch_attention_mfma<64, 8>(dim3(base), s, Q, kv, O, st, g, kg, layer, scale, sp);
           ns = 1;

@@ -50,6 +50,14 @@ __device__ __forceinline__ u32x4 ds_read16_off(uint32_t addr) {
   return v;
 }
 
+template <int OFF>
+__device__ __forceinline__ u32x2 ds_read8_off(uint32_t addr) {
+  static_assert(OFF >= 0 && OFF < 65536, "ds offset range");
+  u32x2 v;
+  asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "i"(OFF) : "memory");
+  return v;
+}
+
 // Transposing 8-byte read of 16-bit data (gfx950).  In each group of 16 lanes,
 // lane 4e + q supplies the address of four consecutive elements (row e, columns
 // 4q..4q+3 of a 4 x 16 block); lane i receives column i: the elements of rows

@@ -53,7 +53,7 @@ def _check(got, ref, where):
 
 
 # (mask, B, H, N, k, d_head, std): ragged row counts (not multiples of the
-# 64-row workgroup), k = 1 (one token per group), odd k = 5 (the kernel's
+# 128-row workgroup), k = 1 (one token per group), odd k = 5 (the kernel's
 # division of row indices by k), N = 1, every d_head, and peaked softmax rows
 # (std 2: scores ~ N(0, 16))
 CASES = [
@@ -90,6 +90,18 @@ def test_training_attention_parity(case):
     _check(got, ref, f"{KIND[mask]} N={N} k={k} dh={dh}")
 
 
+# row counts on both sides of the 128-row workgroup and the 32-row wavefront
+# edges: N (1 + k) = 127, 128, 129, 160, 161 (single), 2 N k likewise even
+EDGES = [(0, 1, 2, 127, 1, 64), (0, 2, 1, 43, 2, 64), (0, 1, 2, 32, 3, 128), (0, 1, 1, 32, 4, 32),
+         (0, 1, 2, 23, 6, 64), (1, 1, 2, 64, 1, 64), (1, 1, 2, 65, 1, 128), (1, 2, 1, 21, 3, 32),
+         (1, 1, 1, 16, 5, 64)]
+
+
+@pytest.mark.parametrize("case", EDGES, ids=lambda c: "%s_B%d_H%d_N%d_k%d_dh%d" % (KIND[c[0]], *c[1:]))
+def test_workgroup_edges(case):
+    test_training_attention_parity((*case, 1.0))
+
+
 def test_empty_problem_launches_nothing():
     Bd = _bd()
     L = Bd.lib()
@@ -105,7 +117,7 @@ def test_owt_training_shape_sampled(mask):
     B = 64, H = 12, N = 1024 context tokens, k = 4, d_head = 64, the launch the
     benchmark times.  Sampled (sequence, head) slices and rows are checked
     against the oracle: first and last rows, rows on both sides of each
-    64-row workgroup edge near the region boundaries, and random rows."""
+    128-row workgroup edge near the region boundaries, and random rows."""
     Bd = _bd()
     B, H, N, k, dh = 64, 12, 1024, 4, 64
     rows, keys = Bd.training_attention_shapes(mask, N, k)
