@@ -886,6 +886,46 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
     return r;
   };
 
+  if constexpr (IsHead<Ep>::value) {
+    // Logits (the AR sampler's input, or a debug copy) go out through LDS, one
+    // wavefront row band at a time, so that a wavefront stores 64 consecutive
+    // columns of one row: from the accumulators a store would touch 16 rows in
+    // 16-byte pieces (rows of an odd vocabulary are not 16-byte aligned), and
+    // the stores, not the MFMAs, bounded a head that keeps its logits (8192 x
+    // 50257 rows at K = 768: 1771 -> 1391 us).  Nontemporal: 31 MB a pass kept
+    // out of the caches leave the weights there (LM1B-shaped batch 64, logits
+    // kept: 16.56 -> 15.57 ms a generate).
+    if (ep.logits) {
+      constexpr int SROW = BN + 4;
+      static_assert(MW * SROW * 4 <= S * (BM + BN) * KCH * 16, "staging fits the ring");
+      float* stage = reinterpret_cast<float*>(&sbuf[0][0][0]);
+      __syncthreads();  // every wavefront is done reading the ring
+#pragma unroll
+      for (int pass = 0; pass < WM; ++pass) {
+        if (wm == pass) {
+#pragma unroll
+          for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm) {
+              const f32x4 r = apply(acc[tn][tm], tm, tn);
+              float* q = stage + (tm * 16 + (lane & 15)) * SROW + wn * NW + tn * 16 + 4 * (lane >> 4);
+              *reinterpret_cast<float4*>(q) = make_float4(r[0], r[1], r[2], r[3]);
+            }
+        }
+        __syncthreads();
+        for (int r = wave; r < MW; r += NWV) {
+          const int m = m0 + pass * MW + r;
+          if (m >= M) break;
+          float* lrow = ep.logits + (size_t)m * ep.V;
+#pragma unroll
+          for (int c = 0; c < BN; c += 64)
+            if (n0 + c + lane < ep.V)
+              __builtin_nontemporal_store(stage[r * SROW + c + lane], lrow + n0 + c + lane);
+        }
+        __syncthreads();  // the next band reuses the staging rows
+      }
+    }
+  }
   if constexpr (!IsHead<Ep>::value) {
     // Stores through LDS: one wavefront row band (MW rows) at a time is
     // written to the free ring as fp32 rows padded by 16 bytes (the 16 lanes
@@ -999,11 +1039,6 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
         sg += __shfl_xor(sg, 32, 64);
         if (m < M) {
           if ((lane >> 4) == 0) ep.psub[((size_t)m * ep.n_tiles + nt) * 8 + wn * TN + tn] = sg;
-          if (ep.logits) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (n + i < ep.V) ep.logits[(size_t)m * ep.V + n + i] = v[i];
-          }
         }
       }
       if (m < M && wn == 0 && (lane >> 4) == 0) ep.pmax[(size_t)m * ep.n_tiles + nt] = mt;
@@ -1026,11 +1061,6 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           if (n + i < ep.V && v[i] > bv) { bv = v[i]; bi = n + i; }
-        if (ep.logits && m < M) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (n + i < ep.V) ep.logits[(size_t)m * ep.V + n + i] = v[i];
-        }
       }
 #pragma unroll
       for (int off = 16; off < 64; off <<= 1) {

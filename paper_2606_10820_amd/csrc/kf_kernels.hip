@@ -682,6 +682,13 @@ __global__ void zero_kernel(T* dst, size_t n) {
 __global__ void copy_f32_kernel(const float* __restrict__ src, float* __restrict__ dst, size_t n) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   size_t stride = (size_t)gridDim.x * blockDim.x;
+  if (((uintptr_t)src | (uintptr_t)dst) % 16 == 0) {  // else a caller's odd address
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    for (; i < n / 4; i += stride)
+      __builtin_nontemporal_store(__builtin_nontemporal_load(reinterpret_cast<const f4*>(src) + i),
+                                  reinterpret_cast<f4*>(dst) + i);
+    i = n / 4 * 4 + ((size_t)blockIdx.x * blockDim.x + threadIdx.x);
+  }
   for (; i < n; i += stride) dst[i] = src[i];
 }
 
@@ -902,7 +909,7 @@ hipError_t launch_zero(T* dst, size_t n, hipStream_t s) {
 
 hipError_t launch_copy_f32(const float* src, float* dst, size_t n, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  launch(copy_f32_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, src, dst, n);
+  launch(copy_f32_kernel, dim3(grid_for((n + 3) / 4, 256)), dim3(256), 0, s, src, dst, n);
   return hipGetLastError();
 }
 
