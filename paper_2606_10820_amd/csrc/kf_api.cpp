@@ -550,18 +550,22 @@ int run_step(kf_ctx* c, const StepIn& in) {
   const int Mh = ar ? in.B : in.B * in.k;
   float* logits = (ar || debug) ? reinterpret_cast<float*>(base + p.logits) : nullptr;
   const kf::LnFold lnf{F(p.head_c1), F(p.head_c2), lnst, rms};
-  // The argmax head commits the step itself (its first workgroup, C += nr),
-  // which saves the commit launch; the AR path commits after its sampler.
-  KF_LAUNCH(c, KF_KC_HEAD,
-            kf::gemm_head_ln<T>(Xh, lnf, W(p.head_w), Mh, p.Vpad, V, d, ar ? 2 : 1, g, pval, pidx,
-                                logits, s, ar ? nullptr : st, in.nr));
+  // The head commits the step itself (its first workgroup, C += nr), which
+  // saves the commit launch.
   if (!ar) {
+    KF_LAUNCH(c, KF_KC_HEAD,
+              kf::gemm_head_ln<T>(Xh, lnf, W(p.head_w), Mh, p.Vpad, V, d, g, pval, pidx, logits, s,
+                                  st, in.nr));
     KF_LAUNCH(c, KF_KC_SELECT,
               kf::launch_argmax_select(pval, pidx, p.n_tiles, g, st, in.od, s, in.nr));
   } else {
+    float* psum = reinterpret_cast<float*>(pidx);  // the same [rows][n_tiles] words
+    KF_LAUNCH(c, KF_KC_HEAD,
+              kf::gemm_head_cdf<T>(Xh, lnf, W(p.head_w), p.Vpad, V, d, g, pval, psum, logits, s, st,
+                                   in.nr));
     KF_LAUNCH(c, KF_KC_SELECT,
-              kf::launch_icdf_select(logits, V, in.u_ar, in.seed, g, st, in.od, s));
-    KF_LAUNCH(c, KF_KC_SELECT, kf::launch_commit(st, g, in.nr, s));
+              kf::launch_icdf_select(logits, pval, psum, p.n_tiles, V, in.u_ar, in.seed, g, st,
+                                     in.od, s, in.nr));
   }
   c->last_head_rows = Mh;
   c->last_logits = logits != nullptr;
@@ -646,7 +650,7 @@ int run_rollout(kf_ctx* c, int B, int N, int k, const int32_t* tokens, const flo
     const KfStepGeom gh{B, n, off, nk};  // head rows: the nk rows after `off` of each sequence
     const kf::LnFold lnf{F(p.head_c1), F(p.head_c2), lnst, rms};
     KF_LAUNCH(c, KF_KC_HEAD,
-              kf::gemm_head_ln<T>(Xh, lnf, W(p.head_w), B * nk, p.Vpad, V, d, 1, gh,
+              kf::gemm_head_ln<T>(Xh, lnf, W(p.head_w), B * nk, p.Vpad, V, d, gh,
                                   reinterpret_cast<float*>(base + p.pval),
                                   reinterpret_cast<int*>(base + p.pidx), logits, s));
     KfOutDesc od;

@@ -504,9 +504,29 @@ struct EpHeadSample {
   }
 };
 
+// Head of an autoregressive step, whose token is drawn by the inverse CDF: per
+// (row, 128-column tile) the maximum M_t of the logits and the sum of
+// exp(l - M_t) over the tile's columns (< V), beside the fp32 logits, of which
+// the selection then reads only the tile that its u falls into.
+struct EpHeadCdf {
+  static constexpr bool kStats = false;
+  const float* bias;  // always null: the tied head has no bias
+  float* pmax;        // [M][n_tiles]
+  float* psum;        // [M][n_tiles]
+  float* logits;      // [M][V]
+  int V, n_tiles;
+  KfDevState* st;     // the step's commit, as in EpHead
+  KfStepGeom cg;
+  int cnr;
+};
+
 template <typename Ep>
 struct IsHead {
   static constexpr bool value = false;
+};
+template <>
+struct IsHead<EpHeadCdf> {
+  static constexpr bool value = true;
 };
 template <>
 struct IsHead<EpHead> {
@@ -892,7 +912,8 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
     // columns of one row: from the accumulators a store would touch 16 rows in
     // 16-byte pieces (rows of an odd vocabulary are not 16-byte aligned), and
     // the stores, not the MFMAs, bounded a head that keeps its logits (8192 x
-    // 50257 rows at K = 768: 1771 -> 1391 us).  Nontemporal: 31 MB a pass kept
+    // 50257 rows at K = 768: 1771 -> 1391 us).  Nontemporal: nothing but the
+    // AR selection's one tile per row reads them soon, and 31 MB a pass kept
     // out of the caches leave the weights there (LM1B-shaped batch 64, logits
     // kept: 16.56 -> 15.57 ms a generate).
     if (ep.logits) {
@@ -1043,6 +1064,54 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
       }
       if (m < M && wn == 0 && (lane >> 4) == 0) ep.pmax[(size_t)m * ep.n_tiles + nt] = mt;
     }
+  } else if constexpr (std::is_same<Ep, EpHeadCdf>::value) {
+    __shared__ float redm[WN][BM], reds[WN][BM];
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) {
+      float bv = -INFINITY;
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn) {
+        const int n = n0 + wn * NW + tn * 16 + 4 * (lane >> 4);
+        const f32x4 v = apply(acc[tn][tm], tm, tn);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (n + i < ep.V) bv = fmaxf(bv, v[i]);
+      }
+      bv = fmaxf(bv, __shfl_xor(bv, 16, 64));
+      bv = fmaxf(bv, __shfl_xor(bv, 32, 64));
+      if ((lane >> 4) == 0) redm[wn][wm * MW + tm * 16 + (lane & 15)] = bv;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) {
+      const int mloc = wm * MW + tm * 16 + (lane & 15);
+      float mt = redm[0][mloc];
+#pragma unroll
+      for (int w = 1; w < WN; ++w) mt = fmaxf(mt, redm[w][mloc]);
+      float sum = 0.f;
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn) {
+        const int n = n0 + wn * NW + tn * 16 + 4 * (lane >> 4);
+        const f32x4 v = apply(acc[tn][tm], tm, tn);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (n + i < ep.V) sum += expf(v[i] - mt);
+      }
+      sum += __shfl_xor(sum, 16, 64);
+      sum += __shfl_xor(sum, 32, 64);
+      if ((lane >> 4) == 0) reds[wn][mloc] = sum;
+    }
+    __syncthreads();
+    if (tid < BM && m0 + tid < M) {
+      float mt = redm[0][tid], sum = reds[0][tid];
+#pragma unroll
+      for (int w = 1; w < WN; ++w) {
+        mt = fmaxf(mt, redm[w][tid]);
+        sum += reds[w][tid];
+      }
+      ep.pmax[(size_t)(m0 + tid) * ep.n_tiles + n0 / BN] = mt;
+      ep.psum[(size_t)(m0 + tid) * ep.n_tiles + n0 / BN] = sum;
+    }
   } else {
     // Row-wise argmax over this tile's columns: lane-local, then across the
     // four lane groups holding the same row, then across the WN wavefronts.
@@ -1090,6 +1159,8 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
         ep.pidx[(size_t)m * ep.n_tiles + nt] = bi;
       }
     }
+  }
+  if constexpr (std::is_same<Ep, EpHead>::value || std::is_same<Ep, EpHeadCdf>::value) {
     if (ep.st && blockIdx.x == 0) {
       if (ep.cg.map) {
         for (int b = tid; b < ep.cg.B; b += NT) ep.cg.cs[ep.cg.map[b]] += ep.cnr;
@@ -1577,25 +1648,37 @@ hipError_t gemm_up_ln_rows(const T* Xh, const LnFold& ln, KfStepGeom g, const T*
                               ep, s);
 }
 
+// Row tiles of the head GEMMs over gathered rows.
+template <typename T, int MODE, class Ep>
+hipError_t launch_head(const GemmA& ga, const T* W, int M, int Vpad, int d, const Ep& ep,
+                       hipStream_t s) {
+  if (M <= 32)
+    return launch_tile<T, 32, kHeadTileN, 1, 4, 3, MODE, true>(ga, W, d, M, Vpad, d, ep, s);
+  // 128-row tiles from 129 rows on: each weight tile is read by half as many
+  // workgroups (LM1B-shaped batch 64, 256 head rows: 24.5 -> 19.3 us per head)
+  if (M <= 128)
+    return launch_tile<T, 64, kHeadTileN, 2, 4, 3, MODE, true>(ga, W, d, M, Vpad, d, ep, s);
+  return launch_tile<T, 128, kHeadTileN, 2, 2, 2, MODE, true>(ga, W, d, M, Vpad, d, ep, s);
+}
+
 template <typename T>
 hipError_t gemm_head_ln(const T* Xh, const LnFold& ln, const T* W, int M, int Vpad, int V, int d,
-                        int gather, KfStepGeom g, float* pval, int* pidx, float* logits,
-                        hipStream_t s, KfDevState* commit_st, int commit_nr) {
+                        KfStepGeom g, float* pval, int* pidx, float* logits, hipStream_t s,
+                        KfDevState* commit_st, int commit_nr) {
   if (M <= 0) return hipSuccess;
   EpHead ep{nullptr, pval, pidx, logits, V, Vpad / kHeadTileN, commit_st, g, commit_nr};
-  const GemmA ga{Xh, d, g.B * g.R, ln.c1, ln.c2, ln.lnst, g, ln.rms};
-  auto go = [&](auto mode) {
-    constexpr int MODE = decltype(mode)::value;
-    if (M <= 32)
-      return launch_tile<T, 32, kHeadTileN, 1, 4, 3, MODE, true>(ga, W, d, M, Vpad, d, ep, s);
-    // 128-row tiles from 129 rows on: each weight tile is read by half as many
-    // workgroups (LM1B-shaped batch 64, 256 head rows: 24.5 -> 19.3 us per head)
-    if (M <= 128)
-      return launch_tile<T, 64, kHeadTileN, 2, 4, 3, MODE, true>(ga, W, d, M, Vpad, d, ep, s);
-    return launch_tile<T, 128, kHeadTileN, 2, 2, 2, MODE, true>(ga, W, d, M, Vpad, d, ep, s);
-  };
-  if (gather == 2) return go(std::integral_constant<int, 2>{});
-  return go(std::integral_constant<int, 1>{});
+  return launch_head<T, 1>(GemmA{Xh, d, g.B * g.R, ln.c1, ln.c2, ln.lnst, g, ln.rms}, W, M, Vpad, d,
+                           ep, s);
+}
+
+template <typename T>
+hipError_t gemm_head_cdf(const T* Xh, const LnFold& ln, const T* W, int Vpad, int V, int d,
+                         KfStepGeom g, float* pmax, float* psum, float* logits, hipStream_t s,
+                         KfDevState* commit_st, int commit_nr) {
+  if (g.B <= 0) return hipSuccess;
+  EpHeadCdf ep{nullptr, pmax, psum, logits, V, Vpad / kHeadTileN, commit_st, g, commit_nr};
+  return launch_head<T, 2>(GemmA{Xh, d, g.B * g.R, ln.c1, ln.c2, ln.lnst, g, ln.rms}, W, g.B, Vpad,
+                           d, ep, s);
 }
 
 template <typename T>
@@ -1659,9 +1742,12 @@ hipError_t launch_ln_fold(const T* W, T* Wout, const float* g, const float* beta
   template hipError_t gemm_residual_rows<T>(const T*, bool, KfStepGeom, const T*, int, int, int,   \
                                             const float*, float*, T*, float2*, const SplitWs*,     \
                                             hipStream_t);                                          \
-  template hipError_t gemm_head_ln<T>(const T*, const LnFold&, const T*, int, int, int, int, int, \
+  template hipError_t gemm_head_ln<T>(const T*, const LnFold&, const T*, int, int, int, int,      \
                                       KfStepGeom, float*, int*, float*, hipStream_t, KfDevState*,  \
                                       int);                                                        \
+  template hipError_t gemm_head_cdf<T>(const T*, const LnFold&, const T*, int, int, int,          \
+                                       KfStepGeom, float*, float*, float*, hipStream_t,            \
+                                       KfDevState*, int);                                          \
   template hipError_t gemm_qkv_seq<T>(const T*, const LnFold&, const T*, int, int, const float*,  \
                                       T*, T*, T*, int, int, int, int, int, int, int,               \
                                       const float2*, hipStream_t);                                 \

@@ -290,18 +290,24 @@ template <typename T>
 hipError_t gemm_noise_out(const T* A, const T* W, int M, int d, int K, const float* bias,
                           const T* pos, const T* temb, float* X, T* Xh, float2* lnst,
                           KfStepGeom g, const KfDevState* st, const SplitWs* ws, hipStream_t s);
-// Head over the final LayerNorm of the selected rows (gather: 1 = noise rows
-// of the step, 2 = last real row per sequence): per (row, 128-column tile) the
-// maximum and its lowest column index into pval/pidx [M][Vpad/128]; columns
-// >= V are excluded.  When logits is not null the fp32 logits [M][V] are
-// written as well.  W is the gain-scaled token table [Vpad][d].  With
+// Head over the final LayerNorm of the step's noise rows: per (row, 128-column
+// tile) the maximum and its lowest column index into pval/pidx [M][Vpad/128];
+// columns >= V are excluded.  When logits is not null the fp32 logits [M][V]
+// are written as well.  W is the gain-scaled token table [Vpad][d].  With
 // commit_st, the head also commits the step (C += commit_nr, or per slot
 // through g's slot map) once its first workgroup is done: nothing after the
 // layers reads C but the selection, which is then told commit_nr.
 template <typename T>
 hipError_t gemm_head_ln(const T* Xh, const LnFold& ln, const T* W, int M, int Vpad, int V, int d,
-                        int gather, KfStepGeom g, float* pval, int* pidx, float* logits,
-                        hipStream_t s, KfDevState* commit_st = nullptr, int commit_nr = 0);
+                        KfStepGeom g, float* pval, int* pidx, float* logits, hipStream_t s,
+                        KfDevState* commit_st = nullptr, int commit_nr = 0);
+// Head over the last real row of each sequence (an autoregressive step): the
+// fp32 logits [B][V] and, per (row, 128-column tile), their maximum and the sum
+// of exp(l - maximum) into pmax, psum [B][Vpad/128].  Commits like gemm_head_ln.
+template <typename T>
+hipError_t gemm_head_cdf(const T* Xh, const LnFold& ln, const T* W, int Vpad, int V, int d,
+                         KfStepGeom g, float* pmax, float* psum, float* logits, hipStream_t s,
+                         KfDevState* commit_st, int commit_nr);
 // Head of a temperature-scaled sampling pass (teacher targets) over rows
 // row0 .. row0 + M - 1 of the step (all rows are real rows; row r belongs to
 // sequence r / rows_per_seq, temperature tau[r / rows_per_seq]): per launch
@@ -362,15 +368,14 @@ hipError_t launch_argmax_select(const float* pval, const int* pidx, int n_tiles,
                                 const KfDevState* st, KfOutDesc od, hipStream_t s,
                                 int committed = 0);
 
-// Inverse-CDF sampling of one token per sequence from fp32 logits [B][V]:
-// smallest m with F_m > u.  u from u_in [B] or, when null, the Philox stream
-// at position C + nr.
-hipError_t launch_icdf_select(const float* logits, int V, const float* u_in, uint64_t seed,
-                              KfStepGeom g, const KfDevState* st, KfOutDesc od, hipStream_t s);
+// Inverse-CDF sampling of one token per sequence from the head's fp32 logits
+// [B][V] and tile partials (gemm_head_cdf): smallest m with F_m > u.  u from
+// u_in [B] or, when null, the Philox stream at position C + nr, C the context
+// length before the step (what the head has added is committed).
+hipError_t launch_icdf_select(const float* logits, const float* pmax, const float* psum,
+                              int n_tiles, int V, const float* u_in, uint64_t seed, KfStepGeom g,
+                              const KfDevState* st, KfOutDesc od, hipStream_t s, int committed);
 
-// C += nr (end of step): KfDevState::C, or with g.map the committed length of
-// each of the step's sequence slots.
-hipError_t launch_commit(KfDevState* st, KfStepGeom g, int nr, hipStream_t s);
 // Committed length 0 for each of the step's sequence slots (g.map required).
 hipError_t launch_seq_reset(KfStepGeom g, hipStream_t s);
 

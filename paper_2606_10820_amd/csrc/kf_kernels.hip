@@ -354,63 +354,115 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+__device__ inline float wave_max(float v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
+  return v;
+}
+__device__ inline float wave_scan(float v, int lane) {  // inclusive, in lane order
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const float t = __shfl_up(v, off, 64);
+    if (lane >= off) v += t;
+  }
+  return v;
+}
+
 // Inverse-CDF map (Appendix B, strict convention): smallest m with F_m > u,
-// F the CDF of softmax(logits) in token-id order, evaluated as
-// prefix(exp(l - max)) > u * Z in fp32 with a fixed chunked order.
-// One workgroup of 1024 threads per sequence.
-__global__ void __launch_bounds__(1024)
-    icdf_select_kernel(const float* __restrict__ logits, int V, const float* __restrict__ u_in,
-                       uint64_t seed, KfStepGeom g, const KfDevState* st, KfOutDesc od) {
-  __shared__ float red[1024];
-  __shared__ int found;
-  const int b = blockIdx.x, t = threadIdx.x;
-  const float* l = logits + (size_t)b * V;
-  const int C = g.ctx(st, b);
+// F the CDF of softmax(logits) in token-id order, evaluated in fp32 as
+// prefix(exp(l - max)) > u Z.  The head left per 128-column tile the maximum M_t
+// and the sum of exp(l - M_t): one wavefront per sequence scans the tiles'
+// masses exp(M_t - M) sum_t (lane L holds a contiguous run of tiles), then the
+// 128 logits of the crossing tile.  When rounding leaves no crossing (u Z at or
+// above the total) both levels take their last element with positive mass, i.e.
+// the last token with q > 0.  (A workgroup per sequence over all V logits took
+// 71 us at B = 96, V = 50257: three passes of 200 KB a row by one CU; this takes
+// 5.)
+__global__ void __launch_bounds__(64)
+    icdf_select_kernel(const float* __restrict__ logits, const float* __restrict__ pmax,
+                       const float* __restrict__ psum, int nT, int V,
+                       const float* __restrict__ u_in, uint64_t seed, KfStepGeom g,
+                       const KfDevState* st, KfOutDesc od, int committed) {
+  constexpr int TL = 8;  // tiles per lane held in registers (vocabularies up to 65536)
+  const int b = blockIdx.x, lane = threadIdx.x;
+  const int C = g.ctx(st, b) - committed;
   const float u = u_in ? u_in[b] : kf_noise_u(seed, g.slot(b), C + g.nr);
-  const int chunk = (V + 1023) / 1024;
-  const int lo = min(V, t * chunk), hi = min(V, lo + chunk);
+  const float* pm = pmax + (size_t)b * nT;
+  const float* ps = psum + (size_t)b * nT;
+  const int c = (nT + 63) / 64, lo = min(nT, lane * c), hi = min(nT, lo + c);
+  float m[TL], w[TL];
+#pragma unroll
+  for (int i = 0; i < TL; ++i) {  // indices clamped, masked below: one round trip
+    const int t = min(lo + i, nT - 1);
+    m[i] = pm[t];
+    w[i] = ps[t];
+  }
   float mx = -INFINITY;
-  for (int i = lo; i < hi; ++i) mx = fmaxf(mx, l[i]);
-  red[t] = mx;
-  __syncthreads();
-  for (int s = 512; s > 0; s >>= 1) {
-    if (t < s) red[t] = fmaxf(red[t], red[t + s]);
-    __syncthreads();
+#pragma unroll
+  for (int i = 0; i < TL; ++i)
+    if (lo + i < hi) mx = fmaxf(mx, m[i]);
+  for (int t = lo + TL; t < hi; ++t) mx = fmaxf(mx, pm[t]);
+  mx = wave_max(mx);
+  auto mass = [&](float mt, float st_) { return mt == -INFINITY ? 0.f : expf(mt - mx) * st_; };
+  float ls = 0.f;
+#pragma unroll
+  for (int i = 0; i < TL; ++i) {
+    w[i] = lo + i < hi ? mass(m[i], w[i]) : 0.f;
+    ls += w[i];
   }
-  mx = red[0];
-  __syncthreads();
-  float cs = 0.f;
-  for (int i = lo; i < hi; ++i) cs += expf(l[i] - mx);
-  red[t] = cs;
-  if (t == 0) found = 0x7fffffff;
-  __syncthreads();
-  // inclusive scan of chunk sums (Hillis-Steele, fixed order)
-  for (int s = 1; s < 1024; s <<= 1) {
-    float add = (t >= s) ? red[t - s] : 0.f;
-    __syncthreads();
-    red[t] += add;
-    __syncthreads();
-  }
-  const float Z = red[1023];
-  const float target = u * Z;
-  float run = (t > 0) ? red[t - 1] : 0.f;
-  if (run <= target && red[t] > target) {
-    // this chunk holds the crossing (at most one chunk satisfies both)
-    int pick = hi - 1;
-    for (int i = lo; i < hi; ++i) {
-      run += expf(l[i] - mx);
-      if (run > target) { pick = i; break; }
+  for (int t = lo + TL; t < hi; ++t) ls += mass(pm[t], ps[t]);
+  const float incl = wave_scan(ls, lane);
+  const float thr = u * __shfl(incl, 63, 64);
+  // the lane, then the tile, in which the prefix crosses thr
+  const uint64_t cross = __ballot(incl > thr), pos = __ballot(ls > 0.f);
+  const bool fall = cross == 0;
+  const int L = !fall ? __ffsll((unsigned long long)cross) - 1
+                      : (pos ? 63 - __clzll((unsigned long long)pos) : 0);
+  float run = incl - ls, before = run;  // mass before this lane's next tile; before the pick
+  int pick = -1, last = lo;
+  float last_run = run;
+  auto step = [&](int t, float wt) {
+    if (pick < 0) {
+      if (!fall && run + wt > thr) {
+        pick = t;
+        before = run;
+      } else if (wt > 0.f) {
+        last = t;
+        last_run = run;
+      }
+      run += wt;
     }
-    atomicMin(&found, pick);
+  };
+#pragma unroll
+  for (int i = 0; i < TL; ++i)
+    if (lo + i < hi) step(lo + i, w[i]);
+  for (int t = lo + TL; t < hi; ++t) step(t, mass(pm[t], ps[t]));
+  if (pick < 0) {  // fallback, or rounding between the lane scan and the tile scan
+    pick = last;
+    before = last_run;
   }
-  __syncthreads();
-  if (t == 0) {
-    int tok = found;
-    if (tok == 0x7fffffff) {  // rounding left F_V <= u: last token with q > 0
-      tok = V - 1;
-      for (int i = V - 1; i >= 0; --i)
-        if (expf(l[i] - mx) > 0.f) { tok = i; break; }
-    }
+  const int tile = __shfl(pick, L, 64);
+  before = __shfl(before, L, 64);
+  // the tile's 128 logits, two per lane
+  const float mt = pm[tile], sc = expf(mt - mx);
+  const int j = tile * kHeadTileN + 2 * lane;
+  const float* l = logits + (size_t)b * V;
+  const float p0 = j < V ? expf(l[j] - mt) * sc : 0.f;
+  const float p1 = j + 1 < V ? expf(l[j + 1] - mt) * sc : 0.f;
+  const float end = before + wave_scan(p0 + p1, lane);  // prefix through column j + 1
+  const float mid = end - p1;
+  const uint64_t hit = fall ? 0 : __ballot(end > thr);
+  int col;
+  if (hit) {
+    col = __ffsll((unsigned long long)hit) - 1;
+    col = 2 * col + (__shfl(mid, col, 64) > thr ? 0 : 1);
+  } else {
+    const uint64_t p = __ballot(p0 + p1 > 0.f);
+    col = p ? 63 - __clzll((unsigned long long)p) : 0;
+    col = 2 * col + (__shfl(p1, col, 64) > 0.f ? 1 : 0);
+  }
+  if (lane == 0) {
+    const int tok = min(tile * kHeadTileN + col, V - 1);
     od.out[out_index(od, C, g.nr, b, 0)] = tok;
     od.pend[(size_t)g.slot(b) * od.pend_stride] = tok;
   }
@@ -463,12 +515,6 @@ __global__ void __launch_bounds__(256)
 // smallest column j with sum_{i <= j} p_i > u Z, the strict convention.  When
 // rounding leaves no crossing (u Z at or above the total), every level takes
 // its last element with positive mass, i.e. the last token with q > 0.
-__device__ inline float wave_max(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-  return v;
-}
-
 // 8 consecutive elements of a compute-dtype row as floats
 __device__ inline void load8f(const float* p, float (&x)[8]) {
   const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
@@ -635,17 +681,6 @@ __global__ void __launch_bounds__(256)
     jstar = pos ? 63 - __clzll((unsigned long long)pos) : 0;
   }
   if (lane == 0) targets[r] = min(j0 + jstar, V - 1);
-}
-
-// End of step: the real rows' K/V become context (C += nr), for the batch or
-// for each sequence slot of the step.
-__global__ void commit_kernel(KfDevState* st, KfStepGeom g, int nr) {
-  if (!g.map) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) st->C += nr;
-    return;
-  }
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < g.B) g.cs[g.map[b]] += nr;
 }
 
 __global__ void scatter_i32_kernel(int* dst, KfScatter u) {
@@ -838,11 +873,12 @@ hipError_t launch_argmax_select(const float* pval, const int* pidx, int n_tiles,
   return hipGetLastError();
 }
 
-hipError_t launch_icdf_select(const float* logits, int V, const float* u_in, uint64_t seed,
-                              KfStepGeom g, const KfDevState* st, KfOutDesc od, hipStream_t s) {
+hipError_t launch_icdf_select(const float* logits, const float* pmax, const float* psum,
+                              int n_tiles, int V, const float* u_in, uint64_t seed, KfStepGeom g,
+                              const KfDevState* st, KfOutDesc od, hipStream_t s, int committed) {
   if (g.B <= 0) return hipSuccess;
-  launch(icdf_select_kernel, dim3(g.B), dim3(1024), 0, s, logits, V, u_in, seed, g, st,
-                     od);
+  launch(icdf_select_kernel, dim3(g.B), dim3(64), 0, s, logits, pmax, psum, n_tiles, V, u_in, seed,
+         g, st, od, committed);
   return hipGetLastError();
 }
 
@@ -865,11 +901,6 @@ hipError_t launch_teacher_select(const float* pmax, const float* psub, int n_til
   if (M <= 0) return hipSuccess;
   launch(teacher_select_kernel<T>, dim3((M + 3) / 4), dim3(256), 0, s, pmax, psub, n_tiles, V, Xh,
          lnst, W, c1, c2, rms, d, tau, u, row0, M, rows_per_seq, targets, st);
-  return hipGetLastError();
-}
-
-hipError_t launch_commit(KfDevState* st, KfStepGeom g, int nr, hipStream_t s) {
-  launch(commit_kernel, dim3(g.map ? (g.B + 255) / 256 : 1), dim3(256), 0, s, st, g, nr);
   return hipGetLastError();
 }
 
