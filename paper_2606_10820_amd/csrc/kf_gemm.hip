@@ -75,6 +75,13 @@ struct Mfma<float> {
   }
 };
 
+// Two floats rounded to bf16 in one dword (one v_cvt_pk_bf16_f32; converting
+// and combining the halves one by one took four instructions).
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ inline uint32_t pack2(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+}
+
 // ------------------------------------------------------------ epilogues
 // store8(m, n, v): v holds C[m][n .. n+7] with the bias (and a folded
 // LayerNorm) already applied; n is a multiple of 8.  The kernel stages each
@@ -88,12 +95,8 @@ struct Mfma<float> {
 template <typename T>
 __device__ inline void put8(T* p, const float (&v)[8]) {
   if constexpr (sizeof(T) == 2) {
-    uint32_t w[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      w[i] = (uint32_t)__builtin_bit_cast(uint16_t, (bf16)v[2 * i]) |
-             ((uint32_t)__builtin_bit_cast(uint16_t, (bf16)v[2 * i + 1]) << 16);
-    *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
+    *reinterpret_cast<uint4*>(p) =
+        make_uint4(pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4], v[5]), pack2(v[6], v[7]));
   } else {
     reinterpret_cast<float4*>(p)[0] = make_float4(v[0], v[1], v[2], v[3]);
     reinterpret_cast<float4*>(p)[1] = make_float4(v[4], v[5], v[6], v[7]);
@@ -107,11 +110,7 @@ typedef unsigned int u32x2s_t __attribute__((ext_vector_type(2)));
 template <typename T>
 __device__ inline void put8_stream(T* p, const float (&v)[8]) {
   if constexpr (sizeof(T) == 2) {
-    u32x4s_t w;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      w[i] = (uint32_t)__builtin_bit_cast(uint16_t, (bf16)v[2 * i]) |
-             ((uint32_t)__builtin_bit_cast(uint16_t, (bf16)v[2 * i + 1]) << 16);
+    const u32x4s_t w = {pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4], v[5]), pack2(v[6], v[7])};
     __builtin_nontemporal_store(w, reinterpret_cast<u32x4s_t*>(p));
   } else {
     put8(p, v);
@@ -148,6 +147,17 @@ struct EpBias {
       for (int i = 0; i < 8; ++i) v[i] = gelu_f(v[i]);
     }
     put8(out + (size_t)m * ldo + n, v);
+  }
+  // The two halves of store8 for 16-bit tiles staged in LDS (see kHalf): the
+  // values of 4 columns before rounding, and 8 rounded columns to memory.
+  __device__ inline void act4(int, int, f32x4& v) const {
+    if (gelu) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = gelu_f(v[i]);
+    }
+  }
+  __device__ inline void store16(int m, int n, const u32x4& w) const {
+    *reinterpret_cast<u32x4*>(out + (size_t)m * ldo + n) = w;
   }
 };
 
@@ -216,16 +226,25 @@ __device__ inline void rotate8(float (&v)[8], const float2* cs, int dr, int p, i
   }
 }
 
+// The same on 4 consecutive columns e .. e + 3 (e a multiple of 4).
+__device__ inline void rotate4(f32x4& v, const float2* cs, int dr, int p, int e) {
+  if (e < dr) {
+    const float4 t = *reinterpret_cast<const float4*>(cs + (size_t)p * (dr / 2) + e / 2);
+    const f32x4 x = v;
+    v[0] = x[0] * t.x - x[1] * t.y;
+    v[1] = x[0] * t.y + x[1] * t.x;
+    v[2] = x[2] * t.z - x[3] * t.w;
+    v[3] = x[2] * t.w + x[3] * t.z;
+  }
+}
+
 // A run of len <= 4 consecutive elements starting at p, whose element 0 sits
 // a elements into an aligned group of 4: the widest aligned stores.
 template <typename T>
 __device__ inline void put_run4(T* p, int a, const float* v, int len) {
   static_assert(kVBlk == 4, "runs of one value block");
   if constexpr (sizeof(T) == 2) {
-    auto pair = [&](int j) {
-      return (uint32_t)__builtin_bit_cast(uint16_t, (bf16)v[j]) |
-             ((uint32_t)__builtin_bit_cast(uint16_t, (bf16)v[j + 1]) << 16);
-    };
+    auto pair = [&](int j) { return pack2(v[j], v[j + 1]); };
     if (len == 4) {  // a == 0: one 8-byte store, nontemporal (see put8_stream)
       const u32x2s_t w = {pair(0), pair(2)};
       __builtin_nontemporal_store(w, reinterpret_cast<u32x2s_t*>(p));
@@ -331,6 +350,67 @@ struct EpQKV {
       }
     }
   }
+  // store8 and store_col8 on rounded values (see kHalf): w[i] of a column holds
+  // rows m + 2i, m + 2i + 1.
+  __device__ inline void act4(int m, int n, f32x4& v) const {
+    if (!rope) return;
+    const int d = kg.H * kg.dh, which = (n >= d) + (n >= 2 * d), c = n - which * d;
+    if (which == 2) return;
+    const int b = div_u(m, g.R), i = m - b * g.R, h = div_u(c, kg.dh);
+    rotate4(v, rope, kg.dh < 64 ? kg.dh : 64, g.ctx(st, b) + i, c - h * kg.dh);
+  }
+  __device__ inline void store16(int m, int n, const u32x4& w) const {
+    const int d = kg.H * kg.dh;
+    const int which = (n >= d) + (n >= 2 * d), c = n - which * d;
+    if (which == 0) {
+      *reinterpret_cast<u32x4*>(Q + (size_t)m * d + c) = w;
+      return;
+    }
+    const int b = div_u(m, g.R), i = m - b * g.R, slot = g.ctx(st, b) + i;
+    const int h = div_u(c, kg.dh), e = c - h * kg.dh;
+    T* base = kv + kg.page_base(g.slot(b), slot) + kg.head_off(layer, which - 1, h);
+    if (which == 1) {
+      __builtin_nontemporal_store(
+          w, reinterpret_cast<u32x4*>(base + (size_t)((unsigned)slot % kPage) * kg.dh + e));
+    } else {  // value columns of a tile that starts before them
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+        base[KfKvGeom::vt_off(slot, e + r, kg.dh)] =
+            __builtin_bit_cast(T, (uint16_t)(w[r >> 1] >> (16 * (r & 1))));
+    }
+  }
+  __device__ inline void store_col16(int m, int n, const uint32_t (&w)[4], int M) const {
+    const int c = n - 2 * kg.H * kg.dh, h = div_u(c, kg.dh), e = c - h * kg.dh;
+    const unsigned ho = kg.head_off(layer, 1, h);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int mq = m + 4 * q;
+      if (mq >= M) break;
+      int i, slot;
+      T* p = vslot(mq, e, ho, i, slot);
+      if ((slot & 3) == 0 && i + 4 <= g.R && mq + 4 <= M) {
+        const u32x2s_t x = {w[2 * q], w[2 * q + 1]};
+        __builtin_nontemporal_store(x, reinterpret_cast<u32x2s_t*>(p));
+        continue;
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {  // rows mq + 2t, mq + 2t + 1
+        const int mt = mq + 2 * t;
+        if (mt >= M) break;
+        int it, st0;
+        T* pt = vslot(mt, e, ho, it, st0);
+        if ((st0 & 1) == 0 && it + 2 <= g.R && mt + 2 <= M) {
+          *reinterpret_cast<uint32_t*>(pt) = w[2 * q + t];
+          continue;
+        }
+        *pt = __builtin_bit_cast(T, (uint16_t)w[2 * q + t]);
+        if (mt + 1 < M) {
+          T* p1 = vslot(mt + 1, e, ho, it, st0);
+          *p1 = __builtin_bit_cast(T, (uint16_t)(w[2 * q + t] >> 16));
+        }
+      }
+    }
+  }
 };
 template <typename Ep>
 struct HasColumns {
@@ -414,7 +494,31 @@ struct EpQKVSeq {
     if (which == 0) put8(Q + (bh * n + i) * dh + e, v);
     else put8((which == 1 ? K : V) + (bh * ldk + koff + i) * dh + e, v);
   }
+  __device__ inline void act4(int m, int c, f32x4& v) const {
+    if (!rope) return;
+    const int d = H * dh, which = c / d, cc = c - which * d, h = cc / dh;
+    if (which < 2) rotate4(v, rope, dh < 64 ? dh : 64, position(m - m / n * n), cc - h * dh);
+  }
+  __device__ inline void store16(int m, int c, const u32x4& w) const {
+    const int d = H * dh, which = (c >= d) + (c >= 2 * d), cc = c - which * d;
+    const int h = div_u(cc, dh), e = cc - h * dh;
+    const int b = m / n, i = m - b * n;
+    const size_t bh = (size_t)b * H + h;
+    T* p = which == 0 ? Q + (bh * n + i) * dh : (which == 1 ? K : V) + (bh * ldk + koff + i) * dh;
+    *reinterpret_cast<u32x4*>(p + e) = w;
+  }
 };
+// Epilogues that only round to 16 bits and store: the kernel finishes the
+// values in registers and stages the tile in LDS as 16-bit rows, once, instead
+// of as fp32 row bands.
+template <class Ep>
+struct IsHalf : std::false_type {};
+template <>
+struct IsHalf<EpBias<bf16>> : std::true_type {};
+template <>
+struct IsHalf<EpQKV<bf16>> : std::true_type {};
+template <>
+struct IsHalf<EpQKVSeq<bf16>> : std::true_type {};
 
 // Second noise-MLP layer of a whole-sequence forward: noise row m = (b, t, j)
 // (N groups of k per sequence) lands in residual row b*n + off + t*k + j with
@@ -856,6 +960,21 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
       }
     }
   }
+  // Eight wavefronts: the old residual values of every band are loaded here,
+  // into the registers that the operands no longer need, so that the bands wait
+  // for one memory round trip and not for one each.
+  constexpr bool kLate = HasPre<Ep>::value && NWV == 8 && KG == 1 && WM * ENCH <= 4;
+  float xlate[kLate ? WM * ENCH : 1][8];
+  if constexpr (kLate) {
+#pragma unroll
+    for (int p = 0; p < WM; ++p)
+#pragma unroll
+      for (int it = 0; it < ENCH; ++it) {
+        const int c0 = it * NT + tid, c = c0 < MW * ECPR ? c0 : MW * ECPR - 1;
+        const int m = m0 + p * MW + c / ECPR, n = n0 + (c % ECPR) * 8;
+        ep.pre8(m < M ? m : M - 1, n < N ? n : 0, xlate[p * ENCH + it]);
+      }
+  }
   if constexpr (KG == 2) {
     // Group 1's sums (the second half of K) are added to group 0's through
     // LDS: the same order as a two-way split summed by the reduction kernel.
@@ -898,7 +1017,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
     if constexpr (NORM) {
       const float2 st = rst[tm];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) r[i] = st.y * (v[i] - st.x * p1[tn][i]) + p2[tn][i] + pb[tn][i];
+      for (int i = 0; i < 4; ++i) r[i] = st.y * (v[i] - st.x * p1[tn][i]) + (p2[tn][i] + pb[tn][i]);
     } else {
 #pragma unroll
       for (int i = 0; i < 4; ++i) r[i] = v[i] + pb[tn][i];
@@ -947,7 +1066,58 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
       }
     }
   }
-  if constexpr (!IsHead<Ep>::value) {
+  if constexpr (IsHalf<Ep>::value) {
+    // The values finished in registers, the tile staged once in LDS as 16-bit
+    // rows padded by 16 bytes (a column write's 16 rows then hit distinct
+    // banks), read back as 8-column chunks, or as columns for value tiles.
+    // Against fp32 row bands: half the LDS traffic, one barrier pair instead of
+    // one per band, a third fewer instructions.
+    constexpr int HROW = BN + 8;
+    static_assert(BM * HROW * 2 <= S * (BM + BN) * KCH * 16, "staging fits the ring");
+    uint16_t* stage = reinterpret_cast<uint16_t*>(&sbuf[0][0][0]);
+    __syncthreads();  // every wavefront is done reading the ring
+    if (kg == 0) {
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) {
+          f32x4 r = apply(acc[tn][tm], tm, tn);
+          const int rr = wm * MW + tm * 16 + (lane & 15), cc = wn * NW + tn * 16 + 4 * (lane >> 4);
+          ep.act4(m0 + rr < M ? m0 + rr : M - 1, n0 + cc < N ? n0 + cc : 0, r);
+          *reinterpret_cast<uint2*>(stage + rr * HROW + cc) = make_uint2(pack2(r[0], r[1]), pack2(r[2], r[3]));
+        }
+    }
+    __syncthreads();
+    if constexpr (HasColumns<Ep>::value) {
+      if (ep.column_tile(n0)) {  // 8 consecutive rows of one column per lane
+        static_assert(BM % 8 == 0, "whole 8-row groups");
+#pragma unroll
+        for (int c0 = 0; c0 < BM / 8 * BN; c0 += NT) {
+          const int c = c0 + tid, cg = c / BN, cl = c % BN;
+          if (c0 + NT <= BM / 8 * BN || c < BM / 8 * BN) {
+            const uint16_t* q = stage + cg * 8 * HROW + cl;
+            uint32_t w[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              w[r] = (uint32_t)q[2 * r * HROW] | ((uint32_t)q[(2 * r + 1) * HROW] << 16);
+            const int m = m0 + cg * 8, n = n0 + cl;
+            if (m < M && n < N) ep.store_col16(m, n, w, M);
+          }
+        }
+        return;
+      }
+    }
+    constexpr int CPR = BN / 8;
+#pragma unroll
+    for (int c0 = 0; c0 < BM * CPR; c0 += NT) {
+      const int c = c0 + tid, rr = c / CPR, cc = c % CPR;
+      if (c0 + NT <= BM * CPR || c < BM * CPR) {
+        const u32x4 w = *reinterpret_cast<const u32x4*>(stage + rr * HROW + cc * 8);
+        const int m = m0 + rr, n = n0 + cc * 8;
+        if (m < M && n < N) ep.store16(m, n, w);
+      }
+    }
+  } else if constexpr (!IsHead<Ep>::value) {
     // Stores through LDS: one wavefront row band (MW rows) at a time is
     // written to the free ring as fp32 rows padded by 16 bytes (the 16 lanes
     // of a column write then hit distinct banks) and read back as 8-column
@@ -1001,6 +1171,8 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
           v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
           if constexpr (kPre) {
             if (live) ep.store8_pre(m, n, v, xpre[pass * ENCH + c0 / NT]);
+          } else if constexpr (kLate) {
+            if (live) ep.store8_pre(m, n, v, xlate[pass * ENCH + c0 / NT]);
           } else {
             if (live) ep.store8(m, n, v);
           }
@@ -1629,23 +1801,24 @@ hipError_t gemm_qkv_ln(const T* Xh, const LnFold& ln, const T* W, int M, int d, 
                        T* Q, T* kv, KfStepGeom g, KfKvGeom kg, int layer, const KfDevState* st,
                        const float2* rope, hipStream_t s) {
   EpQKV<T> ep{Q, kv, bias, st, g, kg, layer, rope};
-  return dispatch<T, 0, true>(GemmA{Xh, d, M, ln.c1, ln.c2, ln.lnst, g, ln.rms}, W, M, 3 * d, d, ep, s);
+  const GemmA ga{Xh, d, M, ln.c1, ln.c2, ln.lnst, g, ln.rms};
+  return dispatch<T, 0, true>(ga, W, M, 3 * d, d, ep, s);
 }
 
 template <typename T>
 hipError_t gemm_up_ln(const T* Xh, const LnFold& ln, const T* W, int M, int N, int d,
                       const float* bias, T* out, hipStream_t s) {
   EpBias<T> ep{out, N, bias, 1};
-  return dispatch<T, 0, true>(GemmA{Xh, d, M, ln.c1, ln.c2, ln.lnst, KfStepGeom{}, ln.rms}, W, M, N, d, ep,
-                              s);
+  const GemmA ga{Xh, d, M, ln.c1, ln.c2, ln.lnst, KfStepGeom{}, ln.rms};
+  return dispatch<T, 0, true>(ga, W, M, N, d, ep, s);
 }
 
 template <typename T>
 hipError_t gemm_up_ln_rows(const T* Xh, const LnFold& ln, KfStepGeom g, const T* W, int M, int N,
                            int d, const float* bias, T* out, hipStream_t s) {
   EpBias<T> ep{out, N, bias, 1};
-  return dispatch<T, 1, true>(GemmA{Xh, d, g.B * g.R, ln.c1, ln.c2, ln.lnst, g, ln.rms}, W, M, N, d,
-                              ep, s);
+  const GemmA ga{Xh, d, g.B * g.R, ln.c1, ln.c2, ln.lnst, g, ln.rms};
+  return dispatch<T, 1, true>(ga, W, M, N, d, ep, s);
 }
 
 // Row tiles of the head GEMMs over gathered rows.
@@ -1667,8 +1840,8 @@ hipError_t gemm_head_ln(const T* Xh, const LnFold& ln, const T* W, int M, int Vp
                         KfDevState* commit_st, int commit_nr) {
   if (M <= 0) return hipSuccess;
   EpHead ep{nullptr, pval, pidx, logits, V, Vpad / kHeadTileN, commit_st, g, commit_nr};
-  return launch_head<T, 1>(GemmA{Xh, d, g.B * g.R, ln.c1, ln.c2, ln.lnst, g, ln.rms}, W, M, Vpad, d,
-                           ep, s);
+  const GemmA ga{Xh, d, g.B * g.R, ln.c1, ln.c2, ln.lnst, g, ln.rms};
+  return launch_head<T, 1>(ga, W, M, Vpad, d, ep, s);
 }
 
 template <typename T>
@@ -1686,8 +1859,8 @@ hipError_t gemm_qkv_seq(const T* Xh, const LnFold& ln, const T* W, int M, int d,
                         T* Q, T* K, T* V, int n, int ldk, int koff, int H, int N, int k, int round,
                         const float2* rope, hipStream_t s) {
   EpQKVSeq<T> ep{Q, K, V, bias, n, ldk, koff, H, d / H, N, k, round, rope};
-  return dispatch<T, 0, true>(GemmA{Xh, d, M, ln.c1, ln.c2, ln.lnst, KfStepGeom{}, ln.rms}, W, M, 3 * d, d,
-                              ep, s);
+  const GemmA ga{Xh, d, M, ln.c1, ln.c2, ln.lnst, KfStepGeom{}, ln.rms};
+  return dispatch<T, 0, true>(ga, W, M, 3 * d, d, ep, s);
 }
 
 template <typename T>
@@ -1705,8 +1878,8 @@ hipError_t gemm_head_sample(const T* Xh, const LnFold& ln, const T* W, int M, in
                             float* logits, hipStream_t s) {
   if (M <= 0) return hipSuccess;
   EpHeadSample ep{nullptr, pmax, psub, logits, tau, row0, rows_per_seq, V, Vpad / kHeadTileN};
-  const GemmA ga{Xh + (size_t)row0 * d, d, M, ln.c1, ln.c2, ln.lnst + (size_t)row0 * (d / 16),
-                 KfStepGeom{}, ln.rms};
+  const GemmA ga{Xh + (size_t)row0 * d, d, M, ln.c1, ln.c2, ln.lnst + (size_t)row0 * (d / 16), KfStepGeom{},
+           ln.rms};
   if (M <= 32)
     return launch_tile<T, 32, kHeadTileN, 1, 4, 3, 0, true>(ga, W, d, M, Vpad, d, ep, s);
   if (M <= 512)
