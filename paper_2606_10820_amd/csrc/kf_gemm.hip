@@ -16,6 +16,7 @@
 #include <math.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "kf_internal.h"
 #include "kf_lds.h"
@@ -48,6 +49,16 @@ __device__ inline float gelu_f(float x) {
   constexpr float k1 = 0.044715f * k0;
   const float z = x * fmaf(k1, x * x, k0);
   return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(z));
+}
+
+// f(0), ..., f(N - 1) with compile-time indices (instruction offsets).
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
 // n / d for n >= 0 and a wave-uniform d > 0: a shift when d is a power of two
@@ -714,12 +725,20 @@ struct GemmA {
 // its own over half of the K steps; the second group's sums are added to the
 // first's through LDS before the epilogue (grids of at most one workgroup per
 // CU, where the two rings double the operand loads in flight).
+//
+// Large tiles (128 x 128 and 160 x 128 with four wavefronts, two workgroups per
+// CU; 256 x 256 with eight, one per CU) run the K loop with the LDS reads and
+// the loads spread between the MFMAs.  At 64 x 64 of output per wavefront a K
+// step reads 64 KB of LDS instead of the 96 KB of eight wavefronts of 64 x 32.
+constexpr bool large_tile(int area, int waves) {
+  return area > 128 * 128 || (area == 128 * 128 && waves == 4);
+}
 template <typename T, int BM, int BN, int WM, int WN, int S, int MODE, bool NORM, class Ep,
           int KG = 1>
 __global__ void __launch_bounds__(64 * WM * WN * KG)
-    __attribute__((amdgpu_waves_per_eu(WM * WN * KG == 8 ? 4 : 1)))
+    __attribute__((amdgpu_waves_per_eu(large_tile(BM * BN, WM * WN) ? 2 : WM * WN * KG == 8 ? 4 : 1)))
     gemm_kernel(GemmA ga, const T* __restrict__ W, int ldw, int M, int N, int K, Ep ep,
-                int ksplit) {
+                int ksplit, int mlo) {
   constexpr int CH = 16 / (int)sizeof(T);  // elements per 16-byte chunk
   constexpr int BK = KCH * CH;             // K per slab
   constexpr int MW = BM / WM, NW = BN / WN;
@@ -737,22 +756,34 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
   static_assert(KG == 1 || KG == 2, "one or two K groups");
   static_assert(KG == 1 || !IsHead<Ep>::value, "K groups: not with the head epilogues");
 
-  __shared__ u32x4 sbuf[KG][S][(BM + BN) * KCH];
+  // Large tiles: two stages (an even number of K steps), and an epilogue whose
+  // staging may be a little larger than the ring.
+  constexpr bool kBig = large_tile(BM * BN, WM * WN);
+  static_assert(!kBig || (S == 2 && KG == 1), "large tiles: two stages, one K group");
+  constexpr int kRing = (BM + BN) * KCH;  // chunks of a stage
+  constexpr int kStageBytes = !kBig || IsHead<Ep>::value ? 0
+                              : IsHalf<Ep>::value        ? BM * (BN + 8) * 2
+                                                         : MW * (BN + 4) * 4;
+  constexpr int kLds = kStageBytes > KG * S * kRing * 16 ? kStageBytes / 16 : KG * S * kRing;
+  __shared__ u32x4 lds[kLds];
+  u32x4(*const sbuf)[S][kRing] = reinterpret_cast<u32x4(*)[S][kRing]>(&lds[0]);
   __shared__ float2 sStat[NORM ? BM : 1];
 
-  const int tid = threadIdx.x, lane = tid & 63;
+  int tid = threadIdx.x, lane = tid & 63;
   // K group kg (of KG) runs its own ring over its share of the K steps;
   // wave is the wavefront's index inside its group.
   const int kg = KG == 1 ? 0 : (tid >> 6) / NWV;
-  const int wave = KG == 1 ? tid >> 6 : (tid >> 6) % NWV;
+  const int wave = kBig      ? __builtin_amdgcn_readfirstlane(tid >> 6)
+                   : KG == 1 ? tid >> 6
+                             : (tid >> 6) % NWV;
   const int wm = wave / WN, wn = wave % WN;
-  const int gm = (M + BM - 1) / BM, gn = (N + BN - 1) / BN;
+  const int gm = (M - mlo + BM - 1) / BM, gn = (N + BN - 1) / BN;
   // ksplit > 1 only with EpPartial: workgroup (tile, split) takes K steps
   // [split * nk, (split + 1) * nk) and writes its own slice of the parts.
   const int split = (int)blockIdx.x % ksplit;
   int tmi, tni;
   tile_coords((int)blockIdx.x / ksplit, gm, gn, tmi, tni);
-  const int m0 = tmi * BM, n0 = tni * BN;
+  const int m0 = mlo + tmi * BM, n0 = tni * BN;
   const int nk = K / BK / ksplit / KG;  // K steps of this wavefront's group
   const int kbeg = (split * KG + kg) * nk;
   if constexpr (std::is_same<Ep, EpPartial>::value) ep.part += (size_t)split * M * ep.ldp;
@@ -805,16 +836,20 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
 
   // Column constants of this lane's output columns (bias; folded-LayerNorm
   // sums), loaded now so that the epilogue does not wait on memory.
+  // The large tiles load them after the K loop: their registers hold operands.
   f32x4 pb[TN], p1[TN], p2[TN];
+  auto load_columns = [&]() {
 #pragma unroll
-  for (int tn = 0; tn < TN; ++tn) {
-    const int n = n0 + wn * NW + tn * 16 + 4 * (lane >> 4);
-    const int nc = n < N ? n : 0;
-    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-    pb[tn] = ep.bias ? *reinterpret_cast<const f32x4*>(ep.bias + nc) : z;
-    p1[tn] = NORM ? *reinterpret_cast<const f32x4*>(ga.c1 + nc) : z;
-    p2[tn] = NORM ? *reinterpret_cast<const f32x4*>(ga.c2 + nc) : z;
-  }
+    for (int tn = 0; tn < TN; ++tn) {
+      const int n = n0 + wn * NW + tn * 16 + 4 * (lane >> 4);
+      const int nc = n < N ? n : 0;
+      const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+      pb[tn] = ep.bias ? *reinterpret_cast<const f32x4*>(ep.bias + nc) : z;
+      p1[tn] = NORM ? *reinterpret_cast<const f32x4*>(ga.c1 + nc) : z;
+      p2[tn] = NORM ? *reinterpret_cast<const f32x4*>(ga.c2 + nc) : z;
+    }
+  };
+  if constexpr (!kBig) load_columns();
 
   // One 32-wide K slice (half a slab) of this wavefront's operands.
   struct Slice {
@@ -852,7 +887,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
   // partials are loaded before the operand loads are issued (so waiting for
   // them does not wait for the operands) and reduced by the TPR consecutive
   // lanes that share a row.
-  static_assert(!NORM || NT % BM == 0, "whole threads per row for the statistics");
+  static_assert(!NORM || NT >= BM, "at least one thread per row for the statistics");
   constexpr int TPR = NORM ? NT / BM : 1;
   // float4 loads (two partials each) per lane, unrolled: whole rows up to
   // K = 1024; wider rows finish in a loop.
@@ -868,7 +903,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
   // are never consumed (the buffer range returns zeros past its end), and it
   // has landed before the first barrier.
   if constexpr (NORM) {
-    const int r = tid / TPR, gr = m0 + r < M ? m0 + r : M - 1;
+    const int r = tid / TPR, gr = m0 + r < M ? m0 + r : M - 1;  // r < BM, or a row not stored
     prow = reinterpret_cast<const float4*>(ga.lnst + (size_t)map_row<MODE>(gr, ga.g) * (K / 16));
 #pragma unroll
     for (int j = 0; j < PMAX; ++j) {
@@ -925,7 +960,8 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
     }
 #pragma unroll
     for (int off = 1; off < TPR; off <<= 1) b += __shfl_xor(b, off, 64);
-    if (tid % TPR == 0) sStat[tid / TPR] = make_float2(mu, 1.0f / sqrtf(b / (float)K + 1e-5f));
+    if (tid % TPR == 0 && (NT % BM == 0 || tid / TPR < BM))
+      sStat[tid / TPR] = make_float2(mu, 1.0f / sqrtf(b / (float)K + 1e-5f));
   }
   if (nk > S - 1) vm_wait<(S - 1) * PER>();
   else vm_wait<0>();
@@ -934,7 +970,87 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
   read_slice(0, 0, f0);
   lgkm_wait0();
   pin_slice(f0);
-  for (int kt0 = 0; kt0 < nk; kt0 += S) {
+  if constexpr (kBig) {
+    // Two wavefronts per SIMD: the reads of the next slice (and the loads of
+    // step kt + 2) are spread between this slice's MFMAs, so that the wavefronts
+    // released by a barrier do not queue at the LDS with the matrix cores idle.
+    // The weight reads come first and the activation reads after them, into the
+    // registers of activation rows whose MFMAs are done.  256 x 256, K = 4096:
+    // 1.56 us a K step, of which the MFMAs alone take 0.87 and with the loads
+    // 1.28 (16384 x 1024: 127-137 us, of which about 37 are the residual
+    // epilogue's 167 MB).
+    constexpr int NMMA = TN * TM;
+    const uint32_t lrow = (uint32_t)(wave * 8 + lane / 8);
+    const uint32_t lcol = (uint32_t)(((lane & 7) ^ ((lrow >> 1) & 7)) * 16);
+    auto step = [&](int stage, int s, int kt, bool load, const Slice& f, Slice& nx) {
+      const uint32_t so = (uint32_t)((kbeg + kt + 2) * BK * (int)sizeof(T));
+      // Slice 1 of a row is slice 0's chunk with bit 2 flipped.  The empty asm
+      // keeps the four addresses from being held in registers all through.
+      const uint32_t sb = lds_addr(&sbuf[0][stage][0]);
+      uint32_t adA = (rdA[0] ^ (64u * s)) + sb, adW = (rdW[0] ^ (64u * s)) + sb;
+      asm volatile("" : "+v"(adA), "+v"(adW));
+      static_for<NMMA>([&](auto xc) {
+        constexpr int x = decltype(xc)::value;
+        static_for<TM>([&](auto rc) {
+          constexpr int r = decltype(rc)::value;
+          if constexpr (NMMA / 4 + r * (NMMA / 2) / TM == x) nx.b[r] = ds_read16_off<r * 16 * ROWB>(adA);
+        });
+        static_for<TN>([&](auto rc) {
+          constexpr int r = decltype(rc)::value;
+          if constexpr (r * (NMMA / 4) / TN == x)
+            nx.a[r] = ds_read16_off<r * 16 * ROWB>(adW);
+        });
+        if (load) {
+#pragma unroll
+          for (int j = 0; j < PER; ++j)
+            if (j * (NMMA * 3 / 4) / PER == x) {
+              void* dst = &sbuf[0][stage ^ 1][(wave * 8 + RPI * j) * KCH];  // PA RPI = BM
+              if constexpr (NWV == 4) {
+                if (j < PA) dma16(ra, aoff[j < PA ? j : 0], so, dst);
+                else dma16(rw, woff[j < PA ? 0 : j - PA], so, dst);
+              } else {
+                // eight wavefronts hold 128 accumulators each: the row offsets are
+                // recomputed (the empty asm keeps them out of the loop's registers)
+                static_assert(MODE == 0, "large tiles of eight wavefronts read rows in order");
+                uint32_t row = lrow;
+                asm volatile("" : "+v"(row));
+                if (j < PA) {
+                  const uint32_t gr = min(row + (uint32_t)(m0 + RPI * j), (uint32_t)M - 1);
+                  dma16(ra, gr * (uint32_t)(ga.lda * sizeof(T)) + lcol, so, dst);
+                } else {
+                  const uint32_t gr = min(row + (uint32_t)(n0 + RPI * (j - PA)), (uint32_t)N - 1);
+                  dma16(rw, gr * (uint32_t)(ldw * sizeof(T)) + lcol, so, dst);
+                }
+              }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        Mfma<T>::mma(f.a[x % TN], f.b[x / TN], acc[x % TN][x / TN]);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      lgkm_wait0();
+      pin_slice(nx);
+    };
+    auto next = [&]() {  // stage kt + 1 has landed; every read of stage kt is done
+      vm_wait<0>();
+      __builtin_amdgcn_s_barrier();
+    };
+    int kt = 0;
+    for (; kt + 2 < nk; kt += 2) {
+      step(0, 1, kt, false, f0, f1);
+      next();
+      step(1, 0, kt, true, f1, f0);
+      step(1, 1, kt, false, f0, f1);
+      next();
+      step(0, 0, kt + 1, true, f1, f0);
+    }
+    step(0, 1, kt, false, f0, f1);
+    next();
+    step(1, 0, kt, false, f1, f0);
+    step(1, 1, kt, false, f0, f1);
+    mma_slice(f1);
+  }
+  for (int kt0 = kBig ? nk : 0; kt0 < nk; kt0 += S) {
 #pragma unroll
     for (int i = 0; i < S; ++i) {
       const int kt = kt0 + i;
@@ -963,7 +1079,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
   // Eight wavefronts: the old residual values of every band are loaded here,
   // into the registers that the operands no longer need, so that the bands wait
   // for one memory round trip and not for one each.
-  constexpr bool kLate = HasPre<Ep>::value && NWV == 8 && KG == 1 && WM * ENCH <= 4;
+  constexpr bool kLate = HasPre<Ep>::value && NWV == 8 && KG == 1 && !kBig && WM * ENCH <= 4;
   float xlate[kLate ? WM * ENCH : 1][8];
   if constexpr (kLate) {
 #pragma unroll
@@ -1005,6 +1121,12 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
     }
   }
 
+  if constexpr (kBig) {
+    // Nothing of the epilogue's indexing is kept through the K loop.
+    asm volatile("" : "+v"(tid));
+    lane = tid & 63;
+    load_columns();
+  }
   // Folded LayerNorm (if any) and bias for 16x16 tile (tn, tm).  The row
   // statistics of this lane's TM rows are read from LDS once, here.
   float2 rst[NORM ? TM : 1];
@@ -1073,7 +1195,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
     // Against fp32 row bands: half the LDS traffic, one barrier pair instead of
     // one per band, a third fewer instructions.
     constexpr int HROW = BN + 8;
-    static_assert(BM * HROW * 2 <= S * (BM + BN) * KCH * 16, "staging fits the ring");
+    static_assert(BM * HROW * 2 <= kLds * 16, "staging fits the ring");
     uint16_t* stage = reinterpret_cast<uint16_t*>(&sbuf[0][0][0]);
     __syncthreads();  // every wavefront is done reading the ring
     if (kg == 0) {
@@ -1124,12 +1246,23 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
     // row chunks, consecutive lanes taking consecutive chunks.
     constexpr int SROW = BN + 4;  // fp32 words per staged row
     constexpr int CPR = BN / 8;   // chunks per row
-    static_assert(MW * SROW * 4 <= S * (BM + BN) * KCH * 16, "staging fits the ring");
+    static_assert(MW * SROW * 4 <= kLds * 16, "staging fits the ring");
     static_assert((MW * CPR) % 64 == 0, "whole wavefronts per chunk pass");
     float* stage = reinterpret_cast<float*>(&sbuf[0][0][0]);
     __syncthreads();  // every wavefront is done reading the ring
 #pragma unroll
     for (int pass = 0; pass < WM; ++pass) {
+      // Large tiles: a band's old residual values, loaded before the band is staged.
+      constexpr bool kBand = HasPre<Ep>::value && kBig;
+      float xband[kBand ? ENCH : 1][8];
+      if constexpr (kBand) {
+#pragma unroll
+        for (int it = 0; it < ENCH; ++it) {
+          const int c0 = it * NT + tid, c = c0 < MW * ECPR ? c0 : MW * ECPR - 1;
+          const int m = m0 + pass * MW + c / ECPR, n = n0 + (c % ECPR) * 8;
+          ep.pre8(m < M ? m : M - 1, n < N ? n : 0, xband[it]);
+        }
+      }
       if (kg == 0 && wm == pass) {
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn)
@@ -1173,6 +1306,8 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
             if (live) ep.store8_pre(m, n, v, xpre[pass * ENCH + c0 / NT]);
           } else if constexpr (kLate) {
             if (live) ep.store8_pre(m, n, v, xlate[pass * ENCH + c0 / NT]);
+          } else if constexpr (kBand) {
+            if (live) ep.store8_pre(m, n, v, xband[c0 / NT]);
           } else {
             if (live) ep.store8(m, n, v);
           }
@@ -1537,10 +1672,10 @@ hipError_t launch_skinny(const GemmA& ga, const T* W, int M, int N, int K, const
 template <typename T, int BM, int BN, int WM, int WN, int S, int MODE, bool NORM, int KG = 1,
           class Ep>
 hipError_t launch_tile(const GemmA& ga, const T* W, int ldw, int M, int N, int K, const Ep& ep,
-                       hipStream_t s, int ksplit = 1) {
-  const int tiles = ((N + BN - 1) / BN) * ((M + BM - 1) / BM);
+                       hipStream_t s, int ksplit = 1, int mlo = 0) {
+  const int tiles = ((N + BN - 1) / BN) * ((M - mlo + BM - 1) / BM);
   launch((gemm_kernel<T, BM, BN, WM, WN, S, MODE, NORM, Ep, KG>), dim3(tiles * ksplit),
-                     dim3(64 * WM * WN * KG), 0, s, ga, W, ldw, M, N, K, ep, ksplit);
+                     dim3(64 * WM * WN * KG), 0, s, ga, W, ldw, M, N, K, ep, ksplit, mlo);
   return hipGetLastError();
 }
 
@@ -1663,17 +1798,38 @@ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 // Steps of at most this many rows run the skinny kernel (16-bit operands).
 constexpr int kSkinnyRows = 16;
 
+// The time of `tiles` tiles at two workgroups per CU, in fifths of a round: a
+// last round of one workgroup per CU or less takes about three.
+inline int tile_rounds(int tiles) {
+  const int rest = tiles % 512;
+  return tiles / 512 * 5 + (rest == 0 ? 0 : rest <= 256 ? 3 : 5);
+}
+
 // Tile choice: the largest tile that still gives about one workgroup per CU.
 template <typename T, int MODE, bool NORM, class Ep>
-hipError_t dispatch(const GemmA& ga, const T* W, int M, int N, int K, const Ep& ep, hipStream_t s,
-                    const SplitWs* ws = nullptr) {
+hipError_t dispatch(const GemmA& ga, const T* W, int Mend, int N, int K, const Ep& ep, hipStream_t s,
+                    const SplitWs* ws = nullptr, int mlo = 0) {
+  const int M = Mend - mlo;  // rows [mlo, Mend)
   if (M <= 0 || N <= 0) return hipSuccess;
   if constexpr (sizeof(T) == 2) {
-    if (M <= kSkinnyRows && N % 16 == 0 && K % 128 == 0)
+    if (mlo == 0 && M <= kSkinnyRows && N % 16 == 0 && K % 128 == 0)
       return launch_skinny<T, MODE, NORM>(ga, W, M, N, K, ep, s);
   }
   constexpr int kFill = 256;
   if constexpr (!NORM && MODE == 0) {
+    if constexpr (sizeof(T) == 2) {
+      // Two workgroups of four wavefronts per CU; 160 rows where they save a
+      // round (see tile_rounds): residual 11808 x 768, K = 3072 83 -> 61 us and
+      // K = 768 34 -> 27, 16896 x 1024, K = 4096 178 -> 166.  128 rows in four
+      // wavefronts against eight: 16384 x 1024, K = 4096 139 -> 132, 9000 x
+      // 768, K = 3072 52 -> 49.
+      const int t128 = cdiv(M, 128) * cdiv(N, 128), t160 = cdiv(M, 160) * cdiv(N, 128);
+      if (t128 >= kFill && K % (2 * KCH * 8) == 0) {
+        if (6 * tile_rounds(t160) < 5 * tile_rounds(t128))
+          return launch_tile<T, 160, 128, 2, 2, 2, MODE, NORM>(ga, W, K, M, N, K, ep, s);
+        return launch_tile<T, 128, 128, 2, 2, 2, MODE, NORM>(ga, W, K, M, N, K, ep, s);
+      }
+    }
     if (cdiv(M, 128) * cdiv(N, 128) >= kFill)
       return launch_plain<T, 128, 128, 2, 4, 2>(ga, W, M, N, K, ep, s, ws);
     if (cdiv(M, 64) * cdiv(N, 128) >= kFill)
@@ -1684,10 +1840,30 @@ hipError_t dispatch(const GemmA& ga, const T* W, int M, int N, int K, const Ep& 
       return launch_plain<T, 32, 64, 2, 2, 4>(ga, W, M, N, K, ep, s, ws);
     return launch_plain<T, 32, 32, 2, 2, 4>(ga, W, M, N, K, ep, s, ws);
   } else {
+    if constexpr (sizeof(T) == 2 && MODE == 0) {
+      // Two or more whole rounds of 256 x 256 tiles: the rows of the whole
+      // rounds take them, the rest the rule below.  A round's tiles load half
+      // the operand bytes of 128 x 128 ones, and a partial round would cost as
+      // much as a whole one.  (One round only: 4096 x 4096, K = 1024 45 -> 45
+      // us, 4088 x 3072, K = 768 30 -> 33.)
+      const int gn = N / 256, per = gn > 0 ? kFill / gn : 0;  // row tiles of a round
+      const int rounds = per > 0 ? M / 256 / per : 0;
+      if (mlo == 0 && N % 256 == 0 && K % (2 * KCH * 8) == 0 && rounds >= 2) {
+        const int big = rounds * per * 256;
+        hipError_t e = launch_tile<T, 256, 256, 2, 4, 2, MODE, NORM>(ga, W, K, big, N, K, ep, s);
+        if (e != hipSuccess) return e;
+        return dispatch<T, MODE, NORM>(ga, W, M, N, K, ep, s, ws, big);
+      }
+      // Four wavefronts per 128 x 128 tile where K is long enough for the
+      // lighter LDS reads to pay for a longer epilogue (16896 x 3072, K = 1024
+      // 139 -> 132 us; 9000 x 2304, K = 768 46.9 -> 47.8).
+      if (cdiv(M, 128) * cdiv(N, 128) >= kFill && K >= 1024 && K % (2 * KCH * 8) == 0)
+        return launch_tile<T, 128, 128, 2, 2, 2, MODE, NORM>(ga, W, K, Mend, N, K, ep, s, 1, mlo);
+    }
     if (cdiv(M, 128) * cdiv(N, 128) >= kFill)
-      return launch_tile<T, 128, 128, 2, 4, 2, MODE, NORM>(ga, W, K, M, N, K, ep, s);
+      return launch_tile<T, 128, 128, 2, 4, 2, MODE, NORM>(ga, W, K, Mend, N, K, ep, s, 1, mlo);
     if (cdiv(M, 64) * cdiv(N, 128) >= kFill)
-      return launch_tile<T, 64, 128, 2, 4, 3, MODE, NORM>(ga, W, K, M, N, K, ep, s);
+      return launch_tile<T, 64, 128, 2, 4, 3, MODE, NORM>(ga, W, K, Mend, N, K, ep, s, 1, mlo);
     {
       // three quarters of a workgroup per CU or more in 64 x 96 tiles: two K
       // groups of four wavefronts (both rings: 120 KB of LDS).  At M = 512
@@ -1695,7 +1871,7 @@ hipError_t dispatch(const GemmA& ga, const T* W, int M, int N, int K, const Ep& 
       // 128 tiles (MLP-up at M = 256) -2.8 % on the OWT-shaped batch 32.
       const int t96 = cdiv(M, 64) * cdiv(N, 96), nk = K / (KCH * 16 / (int)sizeof(T));
       if (N % 96 == 0 && t96 >= 192 && t96 <= kTwoGroupMax && nk % 2 == 0 && nk >= 8)
-        return launch_tile<T, 64, 96, 2, 2, 3, MODE, NORM, 2>(ga, W, K, M, N, K, ep, s);
+        return launch_tile<T, 64, 96, 2, 2, 3, MODE, NORM, 2>(ga, W, K, Mend, N, K, ep, s, 1, mlo);
     }
     // The smaller tiles take two K groups on grids of half to one workgroup
     // per CU as well (the QKV and MLP-up GEMMs at OWT-shaped batch 8 and 16:
@@ -1706,17 +1882,17 @@ hipError_t dispatch(const GemmA& ga, const T* W, int M, int N, int K, const Ep& 
     };
     if (cdiv(M, 64) * cdiv(N, 64) >= kFill * 3 / 4) {
       if (two(cdiv(M, 64) * cdiv(N, 64)))
-        return launch_tile<T, 64, 64, 2, 2, 3, MODE, NORM, 2>(ga, W, K, M, N, K, ep, s);
-      return launch_tile<T, 64, 64, 2, 2, 3, MODE, NORM>(ga, W, K, M, N, K, ep, s);
+        return launch_tile<T, 64, 64, 2, 2, 3, MODE, NORM, 2>(ga, W, K, Mend, N, K, ep, s, 1, mlo);
+      return launch_tile<T, 64, 64, 2, 2, 3, MODE, NORM>(ga, W, K, Mend, N, K, ep, s, 1, mlo);
     }
     if (cdiv(M, 32) * cdiv(N, 64) >= kFill * 3 / 4) {
       if (two(cdiv(M, 32) * cdiv(N, 64)))
-        return launch_tile<T, 32, 64, 2, 2, 4, MODE, NORM, 2>(ga, W, K, M, N, K, ep, s);
-      return launch_tile<T, 32, 64, 2, 2, 4, MODE, NORM>(ga, W, K, M, N, K, ep, s);
+        return launch_tile<T, 32, 64, 2, 2, 4, MODE, NORM, 2>(ga, W, K, Mend, N, K, ep, s, 1, mlo);
+      return launch_tile<T, 32, 64, 2, 2, 4, MODE, NORM>(ga, W, K, Mend, N, K, ep, s, 1, mlo);
     }
     if (two(cdiv(M, 32) * cdiv(N, 32)))
-      return launch_tile<T, 32, 32, 2, 2, 4, MODE, NORM, 2>(ga, W, K, M, N, K, ep, s);
-    return launch_tile<T, 32, 32, 2, 2, 4, MODE, NORM>(ga, W, K, M, N, K, ep, s);
+      return launch_tile<T, 32, 32, 2, 2, 4, MODE, NORM, 2>(ga, W, K, Mend, N, K, ep, s, 1, mlo);
+    return launch_tile<T, 32, 32, 2, 2, 4, MODE, NORM>(ga, W, K, Mend, N, K, ep, s, 1, mlo);
   }
 }
 
@@ -1831,7 +2007,9 @@ hipError_t launch_head(const GemmA& ga, const T* W, int M, int Vpad, int d, cons
   // workgroups (LM1B-shaped batch 64, 256 head rows: 24.5 -> 19.3 us per head)
   if (M <= 128)
     return launch_tile<T, 64, kHeadTileN, 2, 4, 3, MODE, true>(ga, W, d, M, Vpad, d, ep, s);
-  return launch_tile<T, 128, kHeadTileN, 2, 2, 2, MODE, true>(ga, W, d, M, Vpad, d, ep, s);
+  if (d % (2 * KCH * 16 / (int)sizeof(T)) == 0)
+    return launch_tile<T, 128, kHeadTileN, 2, 2, 2, MODE, true>(ga, W, d, M, Vpad, d, ep, s);
+  return launch_tile<T, 128, kHeadTileN, 2, 4, 2, MODE, true>(ga, W, d, M, Vpad, d, ep, s);
 }
 
 template <typename T>
@@ -1884,7 +2062,9 @@ hipError_t gemm_head_sample(const T* Xh, const LnFold& ln, const T* W, int M, in
     return launch_tile<T, 32, kHeadTileN, 1, 4, 3, 0, true>(ga, W, d, M, Vpad, d, ep, s);
   if (M <= 512)
     return launch_tile<T, 64, kHeadTileN, 2, 4, 3, 0, true>(ga, W, d, M, Vpad, d, ep, s);
-  return launch_tile<T, 128, kHeadTileN, 2, 2, 2, 0, true>(ga, W, d, M, Vpad, d, ep, s);
+  if (d % (2 * KCH * 16 / (int)sizeof(T)) == 0)
+    return launch_tile<T, 128, kHeadTileN, 2, 2, 2, 0, true>(ga, W, d, M, Vpad, d, ep, s);
+  return launch_tile<T, 128, kHeadTileN, 2, 4, 2, 0, true>(ga, W, d, M, Vpad, d, ep, s);
 }
 
 template <typename T>
