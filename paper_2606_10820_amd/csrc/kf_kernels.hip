@@ -139,97 +139,160 @@ __global__ void __launch_bounds__(256)
 // attend causally over slots [0, C + i]: real row i sees the context and real
 // rows <= i, noise row j sees the context, every real row and noise rows <= j
 // (the fully causal layout of Sec. 3.3; mask of the decode window, App. C).
-// Online softmax over 64-key tiles streamed from the per-sequence cache.
-template <typename T, int DH>
-__global__ void __launch_bounds__(256)
-    attention_kernel(const T* __restrict__ Q, const T* __restrict__ kv, T* __restrict__ O,
-                     const KfDevState* st, KfStepGeom g, KfKvGeom kg, int layer, float scale) {
-  constexpr int QB = 16, KT = 64, EPT = DH / 16;
+// fp32 on v_mfma_f32_16x16x4_f32 with the layout of the bf16 kernel:
+//   S^T = K Q^T   A = 16 keys, B = 16 queries; lane group gq feeds columns
+//                 16 c + 4 gq + j to MFMA j of chunk c on both sides, so K and Q
+//                 are read as 16-byte chunks of their rows;
+//   O^T += V^T P^T  a lane holds the probabilities of keys 4 gq .. 4 gq + 3 of a
+//                 16-key group, and one 16-byte read of the value blocks holds
+//                 those four slots of a value row: MFMA j takes key 4 gq + j.
+// No LDS and no barrier until the wavefronts' states are merged: the NW
+// wavefronts take 32-key tiles round-robin.  A decode block is bound by its one
+// memory round trip and the MFMA chains (16 x 32 cycles per 16 keys); with K and
+// V staged in LDS and dot products on the VALU a launch took 16.4 us at 6
+// sequences x 12 heads, d_head 64, contexts of 33 to 81.
+template <int DH, int NW>
+__global__ void __launch_bounds__(64 * NW)
+    attention_f32_kernel(const float* __restrict__ Q, const float* __restrict__ kv,
+                         float* __restrict__ O, const KfDevState* st, KfStepGeom g, KfKvGeom kg,
+                         int layer, float scale) {
+  constexpr int QB = 16, KT = 32, NC = DH / 16;
+  static_assert(kPage % KT == 0, "a key tile lies in one KV page");
+  static_assert(kVBlk == 4, "a value block is one lane's four keys");
   const int H = kg.H, d = H * DH;
   const int b = blockIdx.x / H, h = blockIdx.x % H;
-  const int q0 = g.qoff + blockIdx.y * QB;
-  const int nq = min(QB, g.R - q0);
+  const int q0 = g.qoff + blockIdx.y * QB, nq = min(QB, g.R - q0);
   const int C = g.ctx(st, b), seq = g.slot(b);
   const int nkeys = C + q0 + nq;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, gq = lane >> 4, lq = lane & 15;
+  const int qslot = C + q0 + lq;
 
-  __shared__ float sQ[QB][DH];
-  __shared__ float sK[KT][DH + 1];
-  __shared__ float sV[KT][DH];
-  __shared__ float sP[QB][KT];
-
-  const int tid = threadIdx.x;
-  for (int idx = tid; idx < QB * DH; idx += 256) {
-    int qi = idx / DH, e = idx % DH;
-    sQ[qi][e] = (qi < nq) ? to_f(Q[((size_t)b * g.R + q0 + qi) * d + h * DH + e]) * scale : 0.f;
-  }
-  const int qi = tid >> 4, r16 = tid & 15;
-  const int qslot = C + q0 + qi;
-  float m_run = -INFINITY, l_run = 0.f;
-  float o[EPT];
+  f32x4_t qf[NC];
+  const float* qrow = Q + ((size_t)b * g.R + q0 + (lq < nq ? lq : nq - 1)) * d + h * DH + 4 * gq;
 #pragma unroll
-  for (int c = 0; c < EPT; ++c) o[c] = 0.f;
+  for (int c = 0; c < NC; ++c) qf[c] = *reinterpret_cast<const f32x4_t*>(qrow + 16 * c) * scale;
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x4_t o[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) o[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  static_assert(kPage % KT == 0, "a key tile lies in one KV page");
-  for (int kt0 = 0; kt0 < nkeys; kt0 += KT) {
-    const T* page = kv + kg.page_base(seq, kt0);
-    const T* Kb = page + kg.head_off(layer, 0, h);
-    const T* Vb = page + kg.head_off(layer, 1, h);
-    const int p0 = kt0 % kPage;
-    __syncthreads();
-    for (int idx = tid; idx < KT * DH; idx += 256) {
-      int kk = idx / DH, e = idx % DH, slot = kt0 + kk;
-      float kx = 0.f, vx = 0.f;
-      if (slot < nkeys) {
-        kx = to_f(Kb[(size_t)(p0 + kk) * DH + e]);
-        vx = to_f(Vb[KfKvGeom::vt_off(p0 + kk, e, DH)]);
-      }
-      sK[kk][e] = kx;
-      sV[kk][e] = vx;
+  for (int t0 = w * KT; t0 < nkeys; t0 += NW * KT) {
+    const float* page = kv + kg.page_base(seq, t0);
+    const float* Kb = page + kg.head_off(layer, 0, h);
+    const float* Vb = page + kg.head_off(layer, 1, h);
+    const int pbase = t0 - t0 % kPage;
+    // Keys past the end read the last key (masked below), value slots past the
+    // end the blocks of this page (zeroed below).
+    f32x4_t kf[2][NC], vf[2][NC];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int key = t0 + 16 * u + lq;
+      const float* krow = Kb + (size_t)((key < nkeys ? key : nkeys - 1) - pbase) * DH + 4 * gq;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) kf[u][c] = *reinterpret_cast<const f32x4_t*>(krow + 16 * c);
     }
-    __syncthreads();
-    float sc[4];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        vf[u][c] = *reinterpret_cast<const f32x4_t*>(
+            Vb + KfKvGeom::vt_off(t0 + 16 * u + 4 * gq - pbase, 16 * c + lq, DH));
+    f32x4_t s[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) s[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+          s[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[u][c][j], qf[c][j], s[u], 0, 0, 0);
+    // this lane: query lq, keys t0 + 16 u + 4 gq + j
     float tmax = -INFINITY;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      int key = r16 * 4 + c, slot = kt0 + key;
-      float dot = 0.f;
-#pragma unroll 16
-      for (int e = 0; e < DH; ++e) dot += sQ[qi][e] * sK[key][e];
-      sc[c] = (qi < nq && slot <= qslot) ? dot : -INFINITY;
-      tmax = fmaxf(tmax, sc[c]);
-    }
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int off = 8; off > 0; off >>= 1) tmax = fmaxf(tmax, __shfl_xor(tmax, off, 16));
+      for (int j = 0; j < 4; ++j) {
+        const int key = t0 + 16 * u + 4 * gq + j;
+        s[u][j] = key <= qslot && key < nkeys ? s[u][j] : -INFINITY;
+        tmax = fmaxf(tmax, s[u][j]);
+      }
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
     const float m_new = fmaxf(m_run, tmax);
     const float ref = (m_new == -INFINITY) ? 0.f : m_new;
     const float alpha = __expf(m_run - ref);
     float psum = 0.f;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float p = __expf(sc[c] - ref);
-      sP[qi][r16 * 4 + c] = p;
-      psum += p;
-    }
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int off = 8; off > 0; off >>= 1) psum += __shfl_xor(psum, off, 16);
+      for (int j = 0; j < 4; ++j) {
+        s[u][j] = __expf(s[u][j] - ref);
+        psum += s[u][j];
+      }
+    psum += __shfl_xor(psum, 16, 64);
+    psum += __shfl_xor(psum, 32, 64);
     l_run = l_run * alpha + psum;
     m_run = m_new;
-    __syncthreads();
 #pragma unroll
-    for (int c = 0; c < EPT; ++c) {
-      int e = c * 16 + r16;
-      float acc = o[c] * alpha;
-#pragma unroll 16
-      for (int key = 0; key < KT; ++key) acc += sP[qi][key] * sV[key][e];
-      o[c] = acc;
-    }
-  }
-  if (qi < nq) {
-    T* orow = O + ((size_t)b * g.R + q0 + qi) * d + h * DH;
-    const float inv = 1.0f / l_run;
+    for (int c = 0; c < NC; ++c) o[c] *= alpha;
 #pragma unroll
-    for (int c = 0; c < EPT; ++c) orow[c * 16 + r16] = from_f<T>(o[c] * inv);
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bool in = t0 + 16 * u + 4 * gq + j < nkeys;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? vf[u][c][j] : 0.f, s[u][j], o[c], 0, 0, 0);
+      }
   }
+
+  // merge the wavefronts' states: o[c][j] is query lq, d_head index 16 c + 4 gq + j
+  __shared__ float sm[NW][QB], sl[NW][QB];
+  __shared__ float so[NW][QB][DH + 1];
+  if (gq == 0) {
+    sm[w][lq] = m_run;
+    sl[w][lq] = l_run;
+  }
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) so[w][lq][16 * c + 4 * gq + j] = o[c][j];
+  __syncthreads();
+  constexpr int TPQ = 64 * NW / QB, EPT = DH / TPQ;  // threads per query row, elements each
+  static_assert(DH % TPQ == 0, "whole elements per thread");
+  const int q = threadIdx.x / TPQ;
+  if (q >= nq) return;
+  float M = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) M = fmaxf(M, sm[i][q]);
+  float f[NW], den = 0.f;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    f[i] = (sm[i][q] == -INFINITY) ? 0.f : __expf(sm[i][q] - M);
+    den += f[i] * sl[i][q];
+  }
+  const float inv = 1.0f / den;
+  float* orow = O + ((size_t)b * g.R + q0 + q) * d + h * DH;
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    const int at = e * TPQ + threadIdx.x % TPQ;
+    float acc = 0.f;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) acc += f[i] * so[i][q][at];
+    orow[at] = acc * inv;
+  }
+}
+
+// Contexts of at most 128 keys (four tiles): four wavefronts; longer ones eight.
+template <int DH>
+void launch_attention_f32(dim3 grid, hipStream_t s, const float* Q, const float* kv, float* O,
+                          const KfDevState* st, const KfStepGeom& g, const KfKvGeom& kg, int layer,
+                          float scale) {
+  if (kg.T <= 128)
+    launch((attention_f32_kernel<DH, 4>), grid, dim3(256), 0, s, Q, kv, O, st, g, kg, layer, scale);
+  else
+    launch((attention_f32_kernel<DH, 8>), grid, dim3(512), 0, s, Q, kv, O, st, g, kg, layer, scale);
 }
 
 // Block attention on MFMA (bf16): one workgroup per (sequence, head, block of
@@ -844,24 +907,23 @@ hipError_t launch_attention(const T* Q, const T* kv, T* O, const KfDevState* st,
     }
     return hipGetLastError();
   }
-  dim3 grid(g.B * kg.H, (g.R - g.qoff + 15) / 16);
-  switch (kg.dh) {
-    case 32:
-      launch((attention_kernel<T, 32>), grid, dim3(256), 0, s, Q, kv, O, st, g, kg,
-                         layer, scale);
-      break;
-    case 64:
-      launch((attention_kernel<T, 64>), grid, dim3(256), 0, s, Q, kv, O, st, g, kg,
-                         layer, scale);
-      break;
-    case 128:
-      launch((attention_kernel<T, 128>), grid, dim3(256), 0, s, Q, kv, O, st, g, kg,
-                         layer, scale);
-      break;
-    default:
-      return hipErrorInvalidValue;
+  if constexpr (sizeof(T) == 4) {
+    const dim3 grid(g.B * kg.H, (g.R - g.qoff + 15) / 16);
+    switch (kg.dh) {
+      case 32:
+        launch_attention_f32<32>(grid, s, Q, kv, O, st, g, kg, layer, scale);
+        break;
+      case 64:
+        launch_attention_f32<64>(grid, s, Q, kv, O, st, g, kg, layer, scale);
+        break;
+      case 128:
+        launch_attention_f32<128>(grid, s, Q, kv, O, st, g, kg, layer, scale);
+        break;
+      default:
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
   }
-  return hipGetLastError();
 }
 
 hipError_t launch_argmax_select(const float* pval, const int* pidx, int n_tiles, KfStepGeom g,
