@@ -318,7 +318,13 @@ struct EpQKV {
   // < M) of value column n.  Rows that are consecutive slots of one sequence
   // within one value block are one contiguous run, and consecutive lanes hold
   // consecutive value rows, whose runs are adjacent.
-  __device__ inline bool column_tile(int n0) const { return n0 >= 2 * kg.H * kg.dh; }
+  // On a small grid (M <= 512, bound by latency) they go out like key rows unless
+  // the rows fall into whole blocks: by column a lane computes up to ten slots
+  // one after another there, by row one.
+  __device__ inline bool column_tile(int n0, int M) const {
+    if (n0 < 2 * kg.H * kg.dh) return false;
+    return M > 512 || (sizeof(T) == 2 && g.R % 4 == 0 && g.ctx(st, 0) % 4 == 0);
+  }
   //
   // Every index into v is a compile-time constant (a run-time index would put
   // v in scratch memory): each group of 4 rows is one aligned 4-slot block of
@@ -833,6 +839,16 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
   for (int x = 0; x < TN; ++x)
 #pragma unroll
     for (int y = 0; y < TM; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // fp32 keeps the odd K slices' sums apart: chains of half the length, whose
+  // rounding is what is left of an fp32 model's error.
+  constexpr bool kTwoSums = sizeof(T) == 4 && !kBig && !IsHead<Ep>::value;
+  f32x4 acc1[kTwoSums ? TN : 1][kTwoSums ? TM : 1];
+  if constexpr (kTwoSums) {
+#pragma unroll
+    for (int x = 0; x < TN; ++x)
+#pragma unroll
+      for (int y = 0; y < TM; ++y) acc1[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
 
   // Column constants of this lane's output columns (bias; folded-LayerNorm
   // sums), loaded now so that the epilogue does not wait on memory.
@@ -1069,12 +1085,25 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
           read_slice((i + 1) % S, 0, f0);
         }
         __builtin_amdgcn_sched_barrier(0);
-        mma_slice(f1);
+        if constexpr (kTwoSums) {
+#pragma unroll
+          for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm) Mfma<T>::mma(f1.a[tn], f1.b[tm], acc1[tn][tm]);
+        } else {
+          mma_slice(f1);
+        }
         __builtin_amdgcn_sched_barrier(0);
         lgkm_wait0();
         pin_slice(f0);
       }
     }
+  }
+  if constexpr (kTwoSums) {
+#pragma unroll
+    for (int x = 0; x < TN; ++x)
+#pragma unroll
+      for (int y = 0; y < TM; ++y) acc[x][y] += acc1[x][y];
   }
   // Eight wavefronts: the old residual values of every band are loaded here,
   // into the registers that the operands no longer need, so that the bands wait
@@ -1211,7 +1240,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
     }
     __syncthreads();
     if constexpr (HasColumns<Ep>::value) {
-      if (ep.column_tile(n0)) {  // 8 consecutive rows of one column per lane
+      if (ep.column_tile(n0, M)) {  // 8 consecutive rows of one column per lane
         static_assert(BM % 8 == 0, "whole 8-row groups");
 #pragma unroll
         for (int c0 = 0; c0 < BM / 8 * BN; c0 += NT) {
@@ -1275,7 +1304,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
       }
       __syncthreads();
       bool by_column = false;
-      if constexpr (HasColumns<Ep>::value) by_column = ep.column_tile(n0);
+      if constexpr (HasColumns<Ep>::value) by_column = ep.column_tile(n0, M);
 #pragma unroll
       for (int c0 = 0; c0 < MW * CPR; c0 += NT) {
         const int c = c0 + tid;
@@ -1628,7 +1657,7 @@ __global__ void __launch_bounds__(64 * KW)
   __syncthreads();
   if (wave != 0) return;
   if constexpr (HasColumns<Ep>::value) {
-    if (ep.column_tile(n0)) {  // 8 consecutive rows of one column per lane
+    if (ep.column_tile(n0, M)) {  // 8 consecutive rows of one column per lane
       const int cg = lane >> 4, cl = lane & 15;
       const int m = 8 * cg, n = n0 + cl;
       if (lane < 32 && m < M && n < N) {
@@ -1769,7 +1798,7 @@ hipError_t launch_plain(const GemmA& ga, const T* W, int M, int N, int K, const 
   // (The tiles of up to 64 x 64 only: the larger ones run on grids of 256
   // workgroups or more.)
   constexpr bool kFit2 = BM * BN <= 64 * 64 && 2 * S * (BM + BN) * KCH * 16 <= 160 * 1024;
-  const bool grid2 = tiles >= kTwoGroupMin ? tiles <= kTwoGroupMax : nk < 24;
+  const bool grid2 = tiles >= kTwoGroupMin ? tiles <= kTwoGroupMax : nk < 24 || sizeof(T) == 4;
   const int kg = kFit2 && grid2 && nk % 2 == 0 && nk >= 8 ? 2 : 1;
   const int nkg = nk / kg;
   int ks = 1;
