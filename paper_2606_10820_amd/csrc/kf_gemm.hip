@@ -1873,15 +1873,19 @@ hipError_t dispatch(const GemmA& ga, const T* W, int Mend, int N, int K, const E
       // Two or more whole rounds of 256 x 256 tiles: the rows of the whole
       // rounds take them, the rest the rule below.  A round's tiles load half
       // the operand bytes of 128 x 128 ones, and a partial round would cost as
-      // much as a whole one.  (One round only: 4096 x 4096, K = 1024 45 -> 45
-      // us, 4088 x 3072, K = 768 30 -> 33.)
-      const int gn = N / 256, per = gn > 0 ? kFill / gn : 0;  // row tiles of a round
-      const int rounds = per > 0 ? M / 256 / per : 0;
-      if (mlo == 0 && N % 256 == 0 && K % (2 * KCH * 8) == 0 && rounds >= 2) {
-        const int big = rounds * per * 256;
-        hipError_t e = launch_tile<T, 256, 256, 2, 4, 2, MODE, NORM>(ga, W, K, big, N, K, ep, s);
-        if (e != hipSuccess) return e;
-        return dispatch<T, MODE, NORM>(ga, W, M, N, K, ep, s, ws, big);
+      // much as a whole one.  One workgroup per CU hides no epilogue, so only
+      // MLP-up from K = 1024 on takes them (16896 x 4096: 177 -> 151 + 13 us for
+      // the rest; K = 768 11808 x 3072: 80 -> 66 + 13; QKV with its KV append
+      // 16896 x 3072: 152 -> 148 + 16).
+      if constexpr (std::is_same<Ep, EpBias<T>>::value) {
+        const int gn = N / 256, per = gn > 0 ? kFill / gn : 0;  // row tiles of a round
+        const int rounds = per > 0 ? M / 256 / per : 0;
+        if (mlo == 0 && N % 256 == 0 && K >= 1024 && K % (2 * KCH * 8) == 0 && rounds >= 2) {
+          const int big = rounds * per * 256;
+          hipError_t e = launch_tile<T, 256, 256, 2, 4, 2, MODE, NORM>(ga, W, K, big, N, K, ep, s);
+          if (e != hipSuccess) return e;
+          return dispatch<T, MODE, NORM>(ga, W, M, N, K, ep, s, ws, big);
+        }
       }
       // Four wavefronts per 128 x 128 tile where K is long enough for the
       // lighter LDS reads to pay for a longer epilogue (16896 x 3072, K = 1024

@@ -15,11 +15,12 @@ torch = pytest.importorskip("torch")
 
 
 @pytest.mark.parametrize("d,H,f,B,N,k", [
-    (128, 4, 8192, 64, 60, 4),   # MLP-up: 4096 rows, exactly two rounds of 256 x 256 tiles
-    (128, 4, 8192, 65, 62, 3),   # 4225 rows: two rounds and 129 rows
-    (512, 8, 256, 128, 60, 4),   # 8192 rows: residual GEMMs in 128 x 128 tiles
-    (512, 8, 256, 129, 62, 3),   # 8385 rows: residual GEMMs in 160 x 128 tiles, the last ragged
-    (1024, 16, 256, 25, 58, 5),  # 1575 rows, K = 1024: QKV in 128 x 128 tiles, the last ragged
+    (1024, 16, 8192, 64, 60, 4),  # MLP-up: 4096 rows, exactly two rounds of 256 x 256 tiles
+    (1024, 16, 8192, 65, 62, 3),  # 4225 rows: two rounds and 129 rows
+    (512, 8, 256, 128, 60, 4),    # 8192 rows: residual GEMMs in 128 x 128 tiles
+    (512, 8, 256, 129, 62, 3),    # 8385 rows: residual GEMMs in 160 x 128 tiles, the last ragged
+    (128, 2, 256, 65, 61, 3),     # heads of 195 rows at the shortest K, two slabs
+    (1024, 16, 256, 25, 58, 5),   # 1575 rows, K = 1024: QKV in 128 x 128 tiles, the last ragged
 ])
 def test_large_tiles(d, H, f, B, N, k):
     from paper_2606_10820_amd import binding as Bd
