@@ -592,6 +592,226 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH
   store_row<DH>(O + at, valid, o, ls);
 }
 
+// The same mask with 16 query rows per wavefront (64 per workgroup) on 16x16x32
+// MFMA, one query per lane of a 16-lane group: twice the workgroups and half the
+// serial work of each, which is what bounds a grid of a few workgroups per CU
+// (d_head 64: B = 2, H = 8, N = 215, k = 8, M_D 39 -> 32 us; B = 22, H = 16, N =
+// 495, k = 1, M_D 95 -> 86; d_head 32: B = 1, H = 12, N = 408, k = 2, M_D 22 -> 15).
+//
+// Its tiles' swizzle: 8 consecutive rows of two adjacent chunks (a transposing
+// read of 16 lanes) and 16 consecutive rows of one chunk touch distinct banks.
+template <int DH>
+__device__ inline int swz16(int r) {
+  constexpr int NCH = DH / 8, RP = 128 / DH;
+  const int m = (r / RP) % NCH;
+  return ((m & (NCH / 2 - 1)) << 1) | (m / (NCH / 2));
+}
+__device__ inline float max_xor16(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return max2(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+template <int DH, int S>
+__global__ void __launch_bounds__(256)
+    training_attention16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
+                                const bf16* __restrict__ V, bf16* __restrict__ O, int mask, int N,
+                                int k, uint32_t km, int nq, int ldk, int H, int BH, int o_inter,
+                                float c2) {
+  using G = Geo<DH, S, 4>;
+  constexpr int QB = 64, NDC = DH / 32, NDB = DH / 16;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[S * G::STAGEB];
+
+  // Work order.  Workgroups are dealt to the 8 XCDs round-robin, so XCD x runs
+  // workgroups x, x + 8, ...  Each XCD is given a contiguous run of the item
+  // list (whole heads, one after another), so that the query blocks of one
+  // head share its keys and values through that XCD's L2.
+  const int nqb = (nq + QB - 1) / QB, total = BH * nqb;
+  const int x8 = blockIdx.x & 7, j8 = blockIdx.x >> 3;
+  const Item C = make_item(x8 * (total >> 3) + min(x8, total & 7) + j8, QB, nqb, mask, N, k, km, nq);
+  const int tid = threadIdx.x, lane = tid & 63, gq = lane >> 4, lq = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // DMA: segment w + 4i of a tile is LDS bytes [1024 (w + 4i), +1024); lane L
+  // fills 16 of them, the chunk that the swizzle puts there
+  uint32_t voff[G::SEGW];
+#pragma unroll
+  for (int i = 0; i < G::SEGW; ++i) {
+    const int byte = (w + 4 * i) * 1024 + 16 * lane;
+    const int r = byte / G::ROWB, pc = (byte % G::ROWB) / 16;
+    voff[i] = r * G::ROWB + ((pc ^ swz16<DH>(r)) * 16);
+  }
+  // LDS read offsets of this lane within a tile.  K (MFMA A of S^T): key row
+  // 16g + lq, logical chunk 4c + gq.  V (transposing reads, MFMA A of O^T):
+  // key row 32c + 4gq + lq/4 (+16 for the upper half of the k-slots), d_head
+  // 16db + 4 (lq % 4), i.e. logical chunk 2db + (lq % 4) / 2, byte 8 (lq % 2).
+  uint32_t kofs[NDC], vofs[NDB];
+#pragma unroll
+  for (int c = 0; c < NDC; ++c) kofs[c] = lq * G::ROWB + (((4 * c + gq) ^ swz16<DH>(lq)) * 16);
+  {
+    const int r = 4 * gq + (lq >> 2);
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+      vofs[db] = r * G::ROWB + (((2 * db + ((lq & 3) >> 1)) ^ swz16<DH>(r)) * 16) + (lq & 1) * 8;
+  }
+  const bf16x8_t ones = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f};
+
+  // Tiles past the last one load nothing, so every wavefront issues the same
+  // number of loads per tile.
+  auto issue = [&](int ti, int stage) {
+    const bool live = ti < C.ntiles;
+    const int t0 = live ? C.t0(ti) : 0;
+    const int rows = live ? min(C.end(ti) - t0, kKT) : 0;
+    const size_t off = ((size_t)C.bh * ldk + t0) * DH;
+    const __amdgpu_buffer_rsrc_t rk = make_rsrc(K + off, rows * G::ROWB);
+    const __amdgpu_buffer_rsrc_t rv = make_rsrc(V + off, rows * G::ROWB);
+    unsigned char* st = smem + stage * G::STAGEB;
+#pragma unroll
+    for (int i = 0; i < G::SEGW; ++i) dma16(rk, voff[i], 0, st + (w + 4 * i) * 1024);
+#pragma unroll
+    for (int i = 0; i < G::SEGW; ++i) dma16(rv, voff[i], 0, st + G::TILEB + (w + 4 * i) * 1024);
+  };
+#pragma unroll
+  for (int j = 0; j < S - 1; ++j) issue(j, j);
+
+  // this lane's query row, its Q fragment (MFMA B operand: d_head 32c + 8gq..+7)
+  // and intervals; the wavefront's union (wlo, whi) and intersection (ilo, ihi)
+  // of its 16 rows' intervals per region
+  const int row = C.q0 + 16 * w + lq;
+  const bool valid = row < nq;
+  bf16x8_t qf[NDC];
+  {
+    const bf16* qrow = Q + ((size_t)C.bh * nq + (valid ? row : 0)) * DH + 8 * gq;
+#pragma unroll
+    for (int c = 0; c < NDC; ++c)
+      qf[c] = valid ? __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(qrow + 32 * c))
+                    : bf16x8_t{};
+  }
+  int wlo[3] = {0, 0, 0}, whi[3] = {0, 0, 0}, ilo[3] = {1, 1, 1}, ihi[3] = {0, 0, 0};
+  if (C.q0 + 16 * w < nq)
+    row_bounds(mask, N, k, km, C.q0 + 16 * w, min(C.q0 + 16 * w + 16, nq), wlo, whi, ilo, ihi);
+  const Intervals iv = valid ? row_intervals(mask, N, k, km, row) : no_intervals();
+  // running max m (log2 units); o = the unnormalised O^T; ls = the row sums of
+  // P, formed by the MFMA against a block of ones (each element of ls is the
+  // sum of this lane's query row over the bf16 probabilities that o uses)
+  float m_run = -INFINITY;
+  f32x4_t o[NDB], ls = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < NDB; ++i) o[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  // per-region values of the current tile's region, updated where a region starts
+  int cwlo = 0, cwhi = 0, cilo = 0, cihi = 0, rlo = 0, rhi = 0;
+  for (int ti = 0; ti < C.ntiles; ++ti) {
+    vm_wait<(S - 2) * G::PER>();  // this wavefront's part of tile ti has landed
+    __builtin_amdgcn_s_barrier();  // ... and everyone's; stage (ti - 1) % S is free
+    issue(ti + S - 1, (ti + S - 1) % S);
+    if (ti == 0 || ti == C.b1 || ti == C.b2) {
+      const int rs = (ti >= C.b1) + (ti >= C.b2);
+      cwlo = pick(wlo, rs);
+      cwhi = pick(whi, rs);
+      cilo = pick(ilo, rs);
+      cihi = pick(ihi, rs);
+      rlo = pick(iv.lo, rs);
+      rhi = pick(iv.hi, rs);
+    }
+    const int t0 = C.t0(ti);
+    if (t0 < cwhi && t0 + kKT > cwlo) {  // some row of this wavefront sees the tile
+      const uint32_t kb = lds_addr(smem + (ti % S) * G::STAGEB), vb = kb + G::TILEB;
+      // S^T = K Q^T: lane holds query lq, keys 16g + 4gq + r
+      u32x4 a[4][NDC];
+      static_for<4>([&](auto gg) {
+#pragma unroll
+        for (int c = 0; c < NDC; ++c) a[gg][c] = ds_read16_off<gg * 16 * G::ROWB>(kb + kofs[c]);
+      });
+      lgkm_wait0();
+      // value fragments of all 64 keys, in flight during the S MFMAs and the softmax
+      u32x2 va[2][NDB], vc[2][NDB];
+      static_for<2>([&](auto c) {
+        static_for<NDB>([&](auto db) {
+          va[c][db] = ds_read_tr16_off<c * 32 * G::ROWB>(vb + vofs[db]);
+          vc[c][db] = ds_read_tr16_off<c * 32 * G::ROWB + 16 * G::ROWB>(vb + vofs[db]);
+        });
+      });
+      f32x4_t sc[4];
+#pragma unroll
+      for (int gg = 0; gg < 4; ++gg) {
+        sc[gg] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < NDC; ++c) {
+          pin(a[gg][c]);
+          sc[gg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[gg][c]),
+                                                           qf[c], sc[gg], 0, 0, 0);
+        }
+      }
+      // mask: a tile serves its own region's interval only (its last keys may
+      // spill into the next region, which has tiles of its own)
+      if (!(t0 >= cilo && t0 + kKT <= cihi)) {
+        const unsigned width = rhi > rlo ? (unsigned)(rhi - rlo) : 0u;
+        const int base = t0 + 4 * gq - rlo;
+#pragma unroll
+        for (int gg = 0; gg < 4; ++gg)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if ((unsigned)(base + 16 * gg + r) >= width) sc[gg][r] = -INFINITY;
+      }
+      float mx = max3(max3(sc[0][0], sc[0][1], sc[0][2]), max3(sc[0][3], sc[1][0], sc[1][1]),
+                      max3(sc[1][2], sc[1][3], sc[2][0]));
+      mx = max3(mx, max3(sc[2][1], sc[2][2], sc[2][3]), max3(sc[3][0], sc[3][1], sc[3][2]));
+      mx = max3(mx, sc[3][3], sc[3][3]);
+      mx = max_xor32(max_xor16(mx)) * c2;
+      // rescale only when the row maximum grows by more than 2^8: probabilities
+      // stay below 256, and the same reference serves numerator and denominator
+      const bool grow = mx > m_run + 8.f;
+      if (__builtin_amdgcn_ballot_w64(grow)) {
+        const float mn = grow ? mx : m_run;
+        const float alpha = __builtin_amdgcn_exp2f(m_run - mn);
+        ls *= alpha;
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) o[db] *= alpha;
+        m_run = mn;
+      }
+      const float mref = m_run == -INFINITY ? 0.f : m_run;
+      bf16x8_t pf[2];
+#pragma unroll
+      for (int gg = 0; gg < 4; ++gg)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          pf[gg >> 1][4 * (gg & 1) + r] =
+              (bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[gg][r], c2, -mref));
+      ls = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[0], ls, 0, 0, 0);
+      ls = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[1], ls, 0, 0, 0);
+      // O^T += V^T P^T, keys 0..31 then 32..63
+      lgkm_wait0();
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) {
+          pin(va[c][db]);
+          pin(vc[c][db]);
+          const u32x4 x = {va[c][db].x, va[c][db].y, vc[c][db].x, vc[c][db].y};
+          o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x), pf[c],
+                                                          o[db], 0, 0, 0);
+        }
+    }
+  }
+  vm_wait<0>();  // loads issued for tiles past the last one
+
+  // lane: query lq, d_head 16db + 4gq + r
+  if (valid) {
+    const float inv = __builtin_amdgcn_rcpf(ls[0]);  // ls >= 1: the row maximum's term
+    // O: [B][H][nq][DH], or [B][nq][H][DH] (rows of a residual stream) with o_inter
+    const int ob = C.bh / H, oh = C.bh - ob * H;
+    bf16* orow = O + (o_inter ? (((size_t)ob * nq + row) * H + oh) * DH
+                              : ((size_t)C.bh * nq + row) * DH) + 4 * gq;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) {
+      const f32x2_t lo = {o[db][0] * inv, o[db][1] * inv}, hi = {o[db][2] * inv, o[db][3] * inv};
+      *reinterpret_cast<uint2*>(orow + 16 * db) =
+          make_uint2(__builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2_t)),
+                     __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf16x2_t)));
+    }
+  }
+}
+
 }  // namespace
 
 int training_attention_rows(int mask, int N, int k) {
@@ -603,10 +823,16 @@ int training_attention_keys(int mask, int N, int k) {
 
 namespace {
 
-// Four wavefronts per workgroup: 128 query rows share each tile's transfer.
-// Two (64 rows) measured slower at every grid, small ones included (OWT-shaped
-// M_S, B = 16: 307 us against 270; causal rows at d_head 64, B = 1, R = 1004:
-// 17.1 us against 15.6).
+// Four wavefronts per workgroup: 128 query rows share each tile's transfer; two
+// (64 rows) measured slower or equal on large grids (OWT-shaped M_S, B = 16: 307
+// us against 270).  Below the line on the number of 128-row items 16 rows per
+// wavefront are faster (ratio of the times, 32 over 16 rows: d_head 64 at 160 to
+// 2816 items 1.21, 1.22, 1.13, 1.03, 1.15, 1.06, 1.01, 1.10, at 4056 and more
+// 0.94, 0.93, 0.94, 0.99; d_head 32 at 156 items 1.53, at 1008 and more 0.82 to
+// 1.05; d_head 128 at 420 and more 0.90 and less).  Short sequences over many
+// heads are balanced as they are (384 heads, N = 123: the 24 launches of a
+// self-forcing rollout together 80 us longer with 16 rows), except at d_head 32,
+// where their few tiles leave the 32-row blocks latency-bound (N = 86: 1.05).
 template <int DH, int S>
 hipError_t launch_ta(int mask, int B, int H, int N, int k, const bf16* Q, const bf16* K,
                      const bf16* V, int ldk, bf16* O, int o_inter, float scale, hipStream_t s) {
@@ -618,6 +844,14 @@ hipError_t launch_ta(int mask, int B, int H, int N, int k, const bf16* Q, const 
   // q / k in the kernel by the rounded-up reciprocal: exact while q * k < 2^32
   if ((long long)nq * (k > 1 ? k : 1) >= (1LL << 32)) return hipErrorInvalidValue;
   const uint32_t km = k > 1 ? (uint32_t)(((1ULL << 32) + k - 1) / k) : 0u;
+  if constexpr (DH <= 64) {
+    const bool few = DH == 32 ? grid.x < 512 || N < 128 : grid.x < 3072 && (N >= 256 || BH < 256);
+    if (few) {
+      launch(training_attention16_kernel<DH, S>, dim3((unsigned)((long long)BH * ((nq + 63) / 64))),
+             dim3(256), 0, s, Q, K, V, O, mask, N, k, km, nq, ldk, H, BH, o_inter, c2);
+      return hipGetLastError();
+    }
+  }
   launch(training_attention_kernel<DH, S, NW>, grid, dim3(64 * NW), 0, s, Q, K, V, O, mask, N, k, km,
          nq, ldk, H, BH, o_inter, c2);
   return hipGetLastError();
