@@ -436,9 +436,12 @@ __device__ inline float wave_scan(float v, int lane) {  // inclusive, in lane or
 // prefix(exp(l - max)) > u Z.  The head left per 128-column tile the maximum M_t
 // and the sum of exp(l - M_t): one wavefront per sequence scans the tiles'
 // masses exp(M_t - M) sum_t (lane L holds a contiguous run of tiles), then the
-// 128 logits of the crossing tile.  When rounding leaves no crossing (u Z at or
-// above the total) both levels take their last element with positive mass, i.e.
-// the last token with q > 0.  (A workgroup per sequence over all V logits took
+// 128 logits of the crossing tile.  Every level picks among its elements with
+// positive mass only: the prefixes of a wave scan are sums in different orders,
+// so one can pass u Z by an ulp at an element without mass (a lane past the last
+// tile among them).  When rounding leaves no crossing (u Z at or above the total)
+// a level takes its last element with positive mass, i.e. the last token with
+// q > 0.  (A workgroup per sequence over all V logits took
 // 71 us at B = 96, V = 50257: three passes of 200 KB a row by one CU; this takes
 // 5.)
 __global__ void __launch_bounds__(64)
@@ -477,7 +480,7 @@ __global__ void __launch_bounds__(64)
   const float incl = wave_scan(ls, lane);
   const float thr = u * __shfl(incl, 63, 64);
   // the lane, then the tile, in which the prefix crosses thr
-  const uint64_t cross = __ballot(incl > thr), pos = __ballot(ls > 0.f);
+  const uint64_t cross = __ballot(incl > thr && ls > 0.f), pos = __ballot(ls > 0.f);
   const bool fall = cross == 0;
   const int L = !fall ? __ffsll((unsigned long long)cross) - 1
                       : (pos ? 63 - __clzll((unsigned long long)pos) : 0);
@@ -485,11 +488,11 @@ __global__ void __launch_bounds__(64)
   int pick = -1, last = lo;
   float last_run = run;
   auto step = [&](int t, float wt) {
-    if (pick < 0) {
+    if (pick < 0 && wt > 0.f) {
       if (!fall && run + wt > thr) {
         pick = t;
         before = run;
-      } else if (wt > 0.f) {
+      } else {
         last = t;
         last_run = run;
       }
@@ -514,11 +517,12 @@ __global__ void __launch_bounds__(64)
   const float p1 = j + 1 < V ? expf(l[j + 1] - mt) * sc : 0.f;
   const float end = before + wave_scan(p0 + p1, lane);  // prefix through column j + 1
   const float mid = end - p1;
-  const uint64_t hit = fall ? 0 : __ballot(end > thr);
+  const uint64_t hit = fall ? 0 : __ballot(end > thr && p0 + p1 > 0.f);
   int col;
   if (hit) {
     col = __ffsll((unsigned long long)hit) - 1;
-    col = 2 * col + (__shfl(mid, col, 64) > thr ? 0 : 1);
+    const bool second = !(p0 > 0.f) || (p1 > 0.f && !(mid > thr));
+    col = 2 * col + (int)(__ballot(second) >> col & 1);
   } else {
     const uint64_t p = __ballot(p0 + p1 > 0.f);
     col = p ? 63 - __clzll((unsigned long long)p) : 0;

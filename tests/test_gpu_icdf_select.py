@@ -46,3 +46,53 @@ def test_icdf_select(V, dtype):
             assert toks[b] == O.icdf(O.softmax(logits[b]), float(u[b])), (step, b)
     assert close <= total // 2 + 1
     assert kf.get_state() == (7, 1, B)
+
+
+def _crafted(rng, V):
+    """Logits (exact in bf16) of a few tokens with mass among tokens without any
+    (exp(-200) is 0 in fp32), and uniforms at the CDF's boundaries and up to
+    three fp32 steps to both sides of them."""
+    logits = np.full(V, -200.0, np.float32)
+    at = np.sort(rng.choice(V, rng.integers(2, 40), replace=False))
+    logits[at] = rng.integers(-16, 17, at.size) / 4.0
+    F = np.cumsum(O.softmax(logits.astype(np.float64)))
+    us = [0.0, np.float32(1.0 - 2.0 ** -24)]
+    for m in rng.choice(at, 9):
+        lo = hi = np.float32(F[m])
+        us.append(lo)
+        for _ in range(3):
+            lo, hi = np.nextafter(lo, np.float32(0)), np.nextafter(hi, np.float32(2))
+            us += [lo, hi]
+    us = np.array(us, np.float32)
+    return logits, F, np.where(us < 1, us, us[1])
+
+
+@pytest.mark.parametrize("dtype", [S.DTYPE_FP32, S.DTYPE_BF16], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("V", [257, 8321, 70001])
+def test_only_tokens_with_mass(V, dtype):
+    """At and beside the boundaries of the CDF, where rounding decides, the token
+    has positive probability and its interval of the CDF holds u up to the fp32
+    error of the sums (under 40 terms and 64 tiles: 4e-6 is 64 roundings).  A
+    final-norm gain of 0 makes the logits the table's products with the shift."""
+    from paper_2606_10820_amd import binding as Bd
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    cfg = S.ModelConfig(1, 64, 2, 64, V, 16, dtype)
+    w = S.make_weights(cfg, seed=3)
+    w["lnf_g"][:] = 0.0
+    w["lnf_b"][:] = 0.0
+    w["lnf_b"][0] = 1.0
+    rng = np.random.default_rng(V)
+    kf = None
+    for trial in range(12):
+        logits, F, us = _crafted(rng, V)
+        w["tok_emb"][:, 0] = logits
+        if kf is None:
+            kf = Bd.KForcing(Bd.make_config(1, 64, 2, 64, V, 16, dtype, us.size, 1, 4, Bd.KF_FLAG_DEBUG_LOGITS))
+        kf.load_weights(S.pack_blob(cfg, w))
+        print(f"icdf mass V={V} dtype={dtype} trial {trial}", flush=True)
+        toks = kf.prefill_ar(S.prompts_uniform(5, us.size, 2, V), us).cpu().numpy()
+        assert np.array_equal(kf.debug_logits(us.size).cpu().numpy(), np.tile(logits, (us.size, 1)))
+        assert (logits[toks] > -200).all(), (trial, toks[logits[toks] == -200])
+        below = np.where(toks > 0, F[toks - 1], 0.0)
+        assert (below <= us + 4e-6).all() and (us < F[toks] + 4e-6).all(), trial
