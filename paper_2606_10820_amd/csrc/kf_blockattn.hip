@@ -40,6 +40,7 @@
 #include "kforcing.h"
 #include "kf_internal.h"
 #include "kf_lds.h"
+#include "kf_route.h"
 
 namespace kf {
 namespace {
@@ -195,7 +196,7 @@ __device__ inline int swz(int r) {
 // each from its union's first key in steps of 64; tile ti lies in region
 // (ti >= b1) + (ti >= b2).
 struct Item {
-  int bh, q0, ntiles, b1, b2, lo0, dt1, dt2, hi0, de1, de2;
+  int bh, q0, qe, ntiles, b1, b2, lo0, dt1, dt2, hi0, de1, de2;  // query rows [q0, qe)
   __device__ int t0(int ti) const {
     return lo0 + kKT * ti + (ti >= b1 ? dt1 : 0) + (ti >= b2 ? dt2 : 0);
   }
@@ -203,14 +204,21 @@ struct Item {
 };
 
 // Item t of the (head, query block) list: head t / nqb, its blocks heaviest
-// (latest rows) first.
+// (latest rows) first.  A head's rows are cut into blocks from row 0 on (prow =
+// nq), or each half of them by itself (prow = nq / 2: see launch_ta).
 __device__ inline Item make_item(int t, int qb, int nqb, int mask, int N, int k, uint32_t km,
-                                 int nq) {
+                                 int nq, int prow) {
   Item it;
   it.bh = t / nqb;
-  it.q0 = (nqb - 1 - (t - it.bh * nqb)) * qb;
+  int j = nqb - 1 - (t - it.bh * nqb), r0 = 0;
+  if (prow < nq && 2 * j >= nqb) {
+    r0 = prow;
+    j -= nqb / 2;
+  }
+  it.q0 = r0 + j * qb;
+  it.qe = min(it.q0 + qb, r0 + prow);
   int lo[3], hi[3], ilo[3], ihi[3], nt[3];
-  row_bounds(mask, N, k, km, it.q0, min(it.q0 + qb, nq), lo, hi, ilo, ihi);
+  row_bounds(mask, N, k, km, it.q0, it.qe, lo, hi, ilo, ihi);
 #pragma unroll
   for (int s = 0; s < 3; ++s) nt[s] = (hi[s] - lo[s] + kKT - 1) / kKT;
   it.ntiles = nt[0] + nt[1] + nt[2];
@@ -260,6 +268,7 @@ struct RowSets {
   int wlo[3], whi[3];  // union over the wavefront's rows
   int ilo[3], ihi[3];  // intersection over them
   int lo[3], hi[3];    // this lane's row
+  int glo, ghi;        // keys inside a union that no row of the wavefront sees
 };
 
 // One work item: the unnormalised O^T and row sum of this lane's query row
@@ -362,7 +371,8 @@ __device__ __forceinline__ void attend(unsigned char* smem, const Item& C, const
     const int t0 = C.t0(ti);
     const uint32_t kb = lds_addr(smem + stage * G::STAGEB), vb = kb + G::TILEB;
     stage = stage + 1 == S ? 0 : stage + 1;
-    if (t0 >= cwhi || t0 + kKT <= cwlo) continue;  // no row of this wavefront sees the tile
+    if (t0 >= cwhi || t0 + kKT <= cwlo || (t0 >= rs_.glo && t0 + kKT <= rs_.ghi))
+      continue;  // no row of this wavefront sees the tile
     // S^T = K Q^T: lane holds query lane % 32, keys 32g + 8 (i / 4) + 4 half + i % 4
     u32x4 a[2][NC];
     static_for<2>([&](auto g) {
@@ -495,8 +505,8 @@ template <int DH, int S, int NW>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH <= 64 ? 3 : 2)))
     training_attention_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
                               const bf16* __restrict__ V, bf16* __restrict__ O, int mask, int N,
-                              int k, uint32_t km, int nq, int ldk, int H, int BH, int o_inter,
-                              float c2) {
+                              int k, uint32_t km, int nq, int prow, int ldk, int H, int BH,
+                              int o_inter, float c2) {
   using G = Geo<DH, S, NW>;
   constexpr int NC = DH / 16, QB = 32 * NW;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[S * G::STAGEB];
@@ -505,16 +515,16 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH
   // workgroups x, x + 8, ...  Each XCD is given a contiguous run of the item
   // list (whole heads, one after another), so that the query blocks of one
   // head share its keys and values through that XCD's L2.
-  const int nqb = (nq + QB - 1) / QB, total = BH * nqb;
+  const int nqb = (prow + QB - 1) / QB * (prow < nq ? 2 : 1), total = BH * nqb;
   const int x8 = blockIdx.x & 7, j8 = blockIdx.x >> 3;
-  const Item C = make_item(x8 * (total >> 3) + min(x8, total & 7) + j8, QB, nqb, mask, N, k, km, nq);
+  const Item C = make_item(x8 * (total >> 3) + min(x8, total & 7) + j8, QB, nqb, mask, N, k, km, nq, prow);
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
   // this lane's query row, its Q fragment (MFMA B operand: d_head 16c + 8 half ..
   // + 7) and intervals
   const int wrow = C.q0 + 32 * w, row = wrow + (lane & 31);
-  const bool valid = row < nq;
+  const bool valid = row < C.qe;
   bf16x8_t qf[NC];
   {
     const bf16* qrow = Q + ((size_t)C.bh * nq + (valid ? row : 0)) * DH + 8 * (lane >> 5);
@@ -522,9 +532,18 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH
     for (int c = 0; c < NC; ++c)
       qf[c] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(qrow + 16 * c));
   }
-  RowSets rs = {{0, 0, 0}, {0, 0, 0}, {1, 1, 1}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-  if (wrow < nq)
-    row_bounds(mask, N, k, km, wrow, min(wrow + 32, nq), rs.wlo, rs.whi, rs.ilo, rs.ihi);
+  RowSets rs = {{0, 0, 0}, {0, 0, 0}, {1, 1, 1}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, 0, 0};
+  if (wrow < C.qe)
+    row_bounds(mask, N, k, km, wrow, min(wrow + 32, C.qe), rs.wlo, rs.whi, rs.ilo, rs.ihi);
+  const int wlast = min(wrow + 32, C.qe) - 1;
+  if (mask == KF_MASK_DOUBLE && wrow < N * k && wlast >= N * k) {
+    // Rows of both parts: the last groups' Future-1 rows and the first groups'
+    // Future-2 rows, whose union in the Future-1 keys is nearly all of them.
+    // Without the gap this wavefront multiplied N k / 64 tiles that none of its
+    // rows sees (M_D at d_head 32, 256 heads, N = 400, k = 1: 39 -> 36 us).
+    rs.glo = row_intervals(mask, N, k, km, wlast).hi[1];
+    rs.ghi = row_intervals(mask, N, k, km, wrow).lo[1];
+  }
   if (valid) {
     const Intervals iv = row_intervals(mask, N, k, km, row);
 #pragma unroll
@@ -567,7 +586,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH
   const int q0 = (nqb - 1 - (t - bh * nqb)) * QB;  // heaviest rows first
   const int keys_end = ctx + min(q0 + QB, g.R);
   const int ntiles = (keys_end + kKT - 1) / kKT;
-  const Item C{bh, q0, ntiles, ntiles, ntiles, 0, 0, 0, keys_end, 0, 0};
+  const Item C{bh, q0, 0, ntiles, ntiles, ntiles, 0, 0, 0, keys_end, 0, 0};
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wrow = q0 + 32 * w, row = wrow + (lane & 31);
@@ -577,7 +596,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH
 #pragma unroll
   for (int c = 0; c < NC; ++c)
     qf[c] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(Q + at + 8 * (lane >> 5) + 16 * c));
-  RowSets rs = {{0, 0, 0}, {0, 0, 0}, {1, 1, 1}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+  RowSets rs = {{0, 0, 0}, {0, 0, 0}, {1, 1, 1}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, 0, 0};
   if (wrow < g.R) {
     rs.whi[0] = ctx + min(wrow + 32, g.R);
     rs.ilo[0] = 0;
@@ -627,7 +646,7 @@ __global__ void __launch_bounds__(256)
   // head share its keys and values through that XCD's L2.
   const int nqb = (nq + QB - 1) / QB, total = BH * nqb;
   const int x8 = blockIdx.x & 7, j8 = blockIdx.x >> 3;
-  const Item C = make_item(x8 * (total >> 3) + min(x8, total & 7) + j8, QB, nqb, mask, N, k, km, nq);
+  const Item C = make_item(x8 * (total >> 3) + min(x8, total & 7) + j8, QB, nqb, mask, N, k, km, nq, nq);
   const int tid = threadIdx.x, lane = tid & 63, gq = lane >> 4, lq = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
 
@@ -825,35 +844,25 @@ namespace {
 
 // Four wavefronts per workgroup: 128 query rows share each tile's transfer; two
 // (64 rows) measured slower or equal on large grids (OWT-shaped M_S, B = 16: 307
-// us against 270).  Below the line on the number of 128-row items 16 rows per
-// wavefront are faster (ratio of the times, 32 over 16 rows: d_head 64 at 160 to
-// 2816 items 1.21, 1.22, 1.13, 1.03, 1.15, 1.06, 1.01, 1.10, at 4056 and more
-// 0.94, 0.93, 0.94, 0.99; d_head 32 at 156 items 1.53, at 1008 and more 0.82 to
-// 1.05; d_head 128 at 420 and more 0.90 and less).  Short sequences over many
-// heads are balanced as they are (384 heads, N = 123: the 24 launches of a
-// self-forcing rollout together 80 us longer with 16 rows), except at d_head 32,
-// where their few tiles leave the 32-row blocks latency-bound (N = 86: 1.05).
+// us against 270).  16 rows per wavefront where training_route says so.
 template <int DH, int S>
 hipError_t launch_ta(int mask, int B, int H, int N, int k, const bf16* Q, const bf16* K,
                      const bf16* V, int ldk, bf16* O, int o_inter, float scale, hipStream_t s) {
   constexpr int NW = 4;
   const int nq = training_attention_rows(mask, N, k);
   const int BH = B * H;
-  const dim3 grid((unsigned)((long long)BH * ((nq + 32 * NW - 1) / (32 * NW))));  // one per item
   const float c2 = scale * 1.4426950408889634f;  // scale * log2(e)
   // q / k in the kernel by the rounded-up reciprocal: exact while q * k < 2^32
   if ((long long)nq * (k > 1 ? k : 1) >= (1LL << 32)) return hipErrorInvalidValue;
   const uint32_t km = k > 1 ? (uint32_t)(((1ULL << 32) + k - 1) / k) : 0u;
-  if constexpr (DH <= 64) {
-    const bool few = DH == 32 ? grid.x < 512 || N < 128 : grid.x < 3072 && (N >= 256 || BH < 256);
-    if (few) {
-      launch(training_attention16_kernel<DH, S>, dim3((unsigned)((long long)BH * ((nq + 63) / 64))),
-             dim3(256), 0, s, Q, K, V, O, mask, N, k, km, nq, ldk, H, BH, o_inter, c2);
-      return hipGetLastError();
-    }
+  const TrainingRoute r = training_route(DH, BH, mask == KF_MASK_DOUBLE, N, k, nq);
+  if (!r.rows32) {
+    launch(training_attention16_kernel<DH, S>, dim3((unsigned)((long long)BH * ((nq + 63) / 64))),
+           dim3(256), 0, s, Q, K, V, O, mask, N, k, km, nq, ldk, H, BH, o_inter, c2);
+    return hipGetLastError();
   }
-  launch(training_attention_kernel<DH, S, NW>, grid, dim3(64 * NW), 0, s, Q, K, V, O, mask, N, k, km,
-         nq, ldk, H, BH, o_inter, c2);
+  launch(training_attention_kernel<DH, S, NW>, dim3((unsigned)((long long)BH * r.blocks32)),
+         dim3(64 * NW), 0, s, Q, K, V, O, mask, N, k, km, nq, r.prow, ldk, H, BH, o_inter, c2);
   return hipGetLastError();
 }
 

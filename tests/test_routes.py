@@ -1,0 +1,82 @@
+"""The size rules that choose an attention kernel (csrc/kf_route.h), compiled for
+the host: each shape below goes to the kernel that measured faster there, and the
+shapes of the GPU tests reach the kernels that they are written for."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SOURCE = """
+#include "kf_route.h"
+extern "C" int training(int dh, long long BH, int two, long long N, long long k, int *prow, int *blocks) {
+  const long long nq = two ? 2 * N * k : N + N * k;
+  const kf::TrainingRoute r = kf::training_route(dh, BH, two != 0, N, k, nq);
+  *prow = r.prow;
+  *blocks = r.blocks32;
+  return r.rows32 ? 32 : 16;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    d = tmp_path_factory.mktemp("routes")
+    (d / "r.cpp").write_text(SOURCE)
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2606_10820_amd", "csrc"),
+                    str(d / "r.cpp"), "-o", str(d / "r.so")], check=True)
+    L = ctypes.CDLL(str(d / "r.so"))
+    L.training.argtypes = [ctypes.c_int, ctypes.c_longlong, ctypes.c_int, ctypes.c_longlong, ctypes.c_longlong,
+                           ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]
+
+    def training(dh, BH, mask, N, k):
+        prow, blocks = ctypes.c_int(), ctypes.c_int()
+        rows = L.training(dh, BH, mask, N, k, ctypes.byref(prow), ctypes.byref(blocks))
+        return rows, prow.value, blocks.value
+    L.training_route = training
+    return L
+
+
+# (d_head, heads, mask, N, k, rows per wavefront), time of 32 rows over 16 rows
+@pytest.mark.parametrize("dh,BH,mask,N,k,want", [
+    (64, 192, 0, 1024, 4, 32),   # OWT-shaped training batch: 0.92
+    (64, 384, 0, 123, 2, 32),    # self-forcing rollout, round 1: 0.94
+    (64, 384, 1, 123, 2, 32),    # and round 2: 0.86
+    (64, 1024, 1, 16, 1, 16),    # a quarter of a workgroup's rows: 1.34
+    (64, 512, 0, 16, 8, 16),     # 144 rows, the second workgroup nearly empty: 1.20
+    (64, 512, 0, 86, 4, 16),     # 430 rows: 1.17
+    (64, 256, 1, 100, 4, 16),    # 800 rows: 1.18
+    (64, 512, 0, 300, 2, 16),    # 900 rows: 1.16
+    (64, 108, 0, 1000, 0, 16),   # causal, few workgroups: 1.10
+    (128, 8, 0, 160, 1, 16),     # 24 workgroups: 1.21
+    (128, 8, 1, 300, 4, 16),     # 160 workgroups: 1.99 (blocks across the halves)
+    (128, 512, 0, 215, 4, 32),   # 0.79
+    (128, 384, 0, 16, 2, 16),    # 48 rows: 1.14
+    (128, 4096, 0, 32, 4, 16),   # 160 rows: 1.10
+    (32, 32, 1, 1000, 1, 16),    # 512 workgroups: 16 rows as before
+    (32, 1024, 0, 300, 2, 16),   # 900 rows: 1.13
+    (32, 512, 0, 250, 4, 32),    # 0.80
+])
+def test_training_rows(routes, dh, BH, mask, N, k, want):
+    assert routes.training_route(dh, BH, mask, N, k)[0] == want
+
+
+def test_training_blocks_cover_the_rows_once(routes):
+    """Blocks of 128 rows cut from row 0 on, or from each half of M_D by itself
+    (512 rows a half on): every row in exactly one block."""
+    for mask in (0, 1):
+        for N in (1, 2, 63, 64, 65, 127, 255, 256, 257, 511, 512, 513, 1000):
+            for k in (1, 2, 3, 7):
+                nq = N + N * k if mask == 0 else 2 * N * k
+                _, prow, blocks = routes.training_route(64, 1, mask, N, k)
+                cut = mask == 1 and N * k >= 512
+                assert prow == (N * k if cut else nq)
+                per = -(-prow // 128)
+                assert blocks == per * (nq // prow)
+
+
+def test_gpu_shapes_reach_the_32_row_kernel(routes):
+    from tests import test_gpu_training_attention_grids as G
+    for mask, N, k, dh, BH in G.LARGE + G.HALVES:
+        assert routes.training_route(dh, BH, mask, N, k)[0] == 32, (mask, N, k, dh, BH)
