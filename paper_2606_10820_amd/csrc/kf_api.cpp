@@ -507,7 +507,7 @@ int run_step(kf_ctx* c, const StepIn& in) {
                 kf::gemm_qkv_ln<T>(Xh, ln1, W(y.wqkv), M, d, F(y.bqkv), Q, kv, g, kg, l, st, rope, s));
       KfStepGeom ga = g;
       if (head_only) ga.qoff = in.nr;
-      KF_LAUNCH(c, KF_KC_ATTN, kf::launch_attention<T>(Q, kv, O, st, ga, kg, l, asp, s));
+      KF_LAUNCH(c, KF_KC_ATTN, kf::launch_attention<T>(Q, kv, O, st, ga, kg, l, asp, in.reset, s));
     }
     if (head_only) {
       const int Mh = in.B * in.k;

@@ -232,10 +232,12 @@ struct AttnSplit {
   int entries;  // capacity in entries
   int ns;
 };
-// Block attention over the KV cache for every (sequence, head, query block).
+// Block attention over the KV cache for every (sequence, head, query block); empty:
+// the step starts at an empty context.
 template <typename T>
 hipError_t launch_attention(const T* Q, const T* kv, T* O, const KfDevState* st, KfStepGeom g,
-                            KfKvGeom kg, int layer, const AttnSplit& ws, hipStream_t s);
+                            KfKvGeom kg, int layer, const AttnSplit& ws, bool empty,
+                            hipStream_t s);
 
 // GEMM family: C = epilogue(A[M][K] . W[N][K]^T), fp32 accumulation.
 template <typename T>

@@ -6,6 +6,7 @@
 
 #include "kf_internal.h"
 #include "kf_attn.h"
+#include "kf_route.h"
 
 namespace kf {
 
@@ -835,42 +836,17 @@ hipError_t launch_noise_sinusoid(T* S, const float* noise, uint64_t seed, const 
   return hipGetLastError();
 }
 
-// Decode grids of 64 to 255 query blocks at d_head 64 (batch 6 to 21 at 12
-// heads) run one workgroup of eight wavefronts per block instead of key
-// splits of four-wavefront workgroups and their merge kernel: measured on the
-// OWT-shaped model at batch 16, attention 43.2 -> 31.0 ms per generate (the
-// generate 139.6 -> 130.5 ms).  Smaller grids keep the splits (batch 1 lost
-// 4 % with eight wavefronts and no split), and grids of 256 blocks and more
-// keep four wavefronts (batch 24 and 32 lost 5 %, batch 64 9 %, batch 256
-// 15 % with eight).
-constexpr int kWideMin = 64;
-// Steps of at least this many rows per sequence (prefills, admissions) run the
-// kernel whose tiles serve 128 query rows.  Measured per layer, decode kernel
-// against it: R = 32 at d_head 64, B = 1 10 us (two kernels) against 6, B = 64
-// 8 against 6; R = 20 lies within the noise of itself.  Grids that the
-// eight-wavefront decode kernel takes keep it (B = 1, R = 256: 9 us against 10).
-constexpr int kPrefillRows = 32;
-
 template <typename T>
 hipError_t launch_attention(const T* Q, const T* kv, T* O, const KfDevState* st, KfStepGeom g,
-                            KfKvGeom kg, int layer, const AttnSplit& ws, hipStream_t s) {
+                            KfKvGeom kg, int layer, const AttnSplit& ws, bool empty, hipStream_t s) {
   if (g.B <= 0 || g.R - g.qoff <= 0) return hipSuccess;
   const float scale = 1.0f / sqrtf((float)kg.dh);
   if constexpr (sizeof(T) == 2) {
-    // key splits: enough workgroups for ~512 in flight, each split at least
-    // 128 keys of the full context, within the partial-state workspace
+    const AttentionRoute r =
+        attention_route(kg.dh, g.B, kg.H, g.R, g.qoff, kg.T, ws.o ? ws.entries : 0, empty);
+    if (r.tiled) return launch_prefill_attention(Q, kv, O, st, g, kg, layer, scale, s);
+    int ns = r.ns;
     const int base = g.B * kg.H * ((g.R - g.qoff + 15) / 16);
-    int ns = 1;
-    if (ws.o && base < 256) {
-      ns = 512 / base;
-      ns = ns < kg.T / 128 ? ns : kg.T / 128;
-      ns = ns < 16 ? ns : 16;
-      while (ns > 1 && (long long)g.B * kg.H * g.R * ns > ws.entries) --ns;
-      if (ns < 1) ns = 1;
-    }
-    const bool wide = kg.dh == 64 && ns > 1 && base >= kWideMin;
-    if (g.qoff == 0 && g.R >= kPrefillRows && !wide)
-      return launch_prefill_attention(Q, kv, O, st, g, kg, layer, scale, s);
     AttnSplit sp = ws;
     sp.ns = ns;
     dim3 grid(base * ns);
@@ -882,7 +858,7 @@ hipError_t launch_attention(const T* Q, const T* kv, T* O, const KfDevState* st,
                              O, g, kg.H, sp);
         break;
       case 64:
-        if (wide) {  // eight wavefronts, no key split
+        if (r.wide) {  // eight wavefronts, no key split
           sp.ns = 1;
           launch_attention_mfma<64, 8>(dim3(base), s, Q, kv, O, st, g, kg, layer, scale, sp);
           ns = 1;
@@ -1022,7 +998,7 @@ hipError_t launch_zero_i32(int* dst, size_t n, hipStream_t s) { return launch_ze
                                                KfStepGeom, int, const KfDevState*, float*,          \
                                                hipStream_t);                                        \
   template hipError_t launch_attention<T>(const T*, const T*, T*, const KfDevState*, KfStepGeom,   \
-                                          KfKvGeom, int, const AttnSplit&, hipStream_t);            \
+                                          KfKvGeom, int, const AttnSplit&, bool, hipStream_t);      \
   template hipError_t launch_convert<T>(const float*, T*, size_t, hipStream_t);                    \
   template hipError_t launch_zero<T>(T*, size_t, hipStream_t);                                   \
   template hipError_t launch_embed_group<T>(float*, T*, float2*, const T*, const T*,              \

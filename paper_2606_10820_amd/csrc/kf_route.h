@@ -41,4 +41,62 @@ inline TrainingRoute training_route(int dh, long long BH, bool two_parts, long l
   return {r32, (int)prow, (int)b32};
 }
 
+// Block attention of a step over the paged KV cache (bf16).  Three kernels:
+//   split  one workgroup of four wavefronts (two for contexts of at most 128 keys)
+//          per 16 query rows and key split, ns splits, and a merge kernel if ns > 1
+//   wide   eight wavefronts per 16 query rows, no split
+//   tiled  128 query rows (d_head 128: 64) share each key tile and walk all keys
+struct AttentionRoute {
+  int ns;
+  bool wide, tiled;
+};
+
+// B sequences, H heads, query rows [qoff, R) of each, T keys of capacity; entries:
+// partial states that the split may write (0: none); empty: the step starts at an
+// empty context (a prefill), so that its rows see R keys at most.
+inline AttentionRoute attention_route(int dh, int B, int H, int R, int qoff, int T,
+                                      long long entries, bool empty) {
+  // key splits: enough workgroups for ~512 in flight, each split at least 128
+  // keys of the full context, within the partial-state workspace
+  const long long base = (long long)B * H * ((R - qoff + 15) / 16);
+  int ns = 1;
+  if (entries > 0 && base < 256) {
+    ns = (int)(512 / base);
+    ns = ns < T / 128 ? ns : T / 128;
+    ns = ns < 16 ? ns : 16;
+    while (ns > 1 && (long long)B * H * R * ns > entries) --ns;
+    if (ns < 1) ns = 1;
+  }
+  // Decode grids of 64 to 255 query blocks at d_head 64 (batch 6 to 21 at 12
+  // heads): measured on the OWT-shaped model at batch 16, attention 43.2 -> 31.0
+  // ms per generate (the generate 139.6 -> 130.5 ms).  Smaller grids keep the
+  // splits (batch 1 lost 4 % with eight wavefronts and no split), and grids of 256
+  // blocks and more keep four wavefronts (batch 24 and 32 lost 5 %, batch 64 9 %,
+  // batch 256 15 % with eight).
+  const bool wide = dh == 64 && ns > 1 && base >= 64;
+  // The tiled kernel reads each key R / 128 times where the others read it R / 16
+  // times, but in fewer workgroups, each of which walks every tile.  Its time over
+  // theirs (12 heads, 1 to 64 sequences, 32 to 1000 rows, T = 128 to 1024):
+  //   few keys (a prefill, or T = 128)
+  //     splits in their place         0.65 to 0.95: it saves the merge kernel
+  //     no split, d_head 64           0.28 to 1.06 from 864 query blocks, or 576 of
+  //                                   128 rows and more; fewer 0.91 to 1.18
+  //     no split, d_head 32           0.48 to 0.95 from 1000 blocks; fewer 0.90 to 1.25
+  //     no split, d_head 128          0.28 to 0.97 from 257 blocks; fewer 1.14 to 1.37
+  //   a context of up to T keys (decode blocks of 32 rows and more)
+  //     splits in their place         T = 256 0.69 to 1.05, d_head 32 at 512 0.69 to
+  //                                   1.02, d_head 128 at two splits 0.74 to 0.94;
+  //                                   else up to 2.0 (one sequence, T = 1024)
+  //     no split                      d_head 64 0.26 to 1.04, d_head 128 0.28 to 0.87,
+  //                                   d_head 32 0.34 to 1.04 from 576 blocks (fewer 1.26)
+  bool tiled = qoff == 0 && R >= 32 && !wide;
+  if (tiled && ns > 1)
+    tiled = empty || T <= (dh == 32 ? 512 : 256) || (dh == 128 && ns == 2);
+  else if (tiled && (empty || T <= 128))
+    tiled = dh == 64 ? base >= 864 || (R >= 128 && base >= 576) : base >= (dh == 32 ? 1000 : 257);
+  else if (tiled)
+    tiled = base >= (dh == 32 ? 576 : 256);
+  return {ns, wide, tiled};
+}
+
 }  // namespace kf

@@ -17,6 +17,11 @@ extern "C" int training(int dh, long long BH, int two, long long N, long long k,
   *blocks = r.blocks32;
   return r.rows32 ? 32 : 16;
 }
+extern "C" int attention(int dh, int B, int H, int R, int qoff, int T, int empty, int *ns) {
+  const kf::AttentionRoute r = kf::attention_route(dh, B, H, R, qoff, T, 8192, empty != 0);
+  *ns = r.ns;
+  return r.tiled ? 2 : r.wide ? 1 : 0;
+}
 """
 
 
@@ -35,6 +40,11 @@ def routes(tmp_path_factory):
         rows = L.training(dh, BH, mask, N, k, ctypes.byref(prow), ctypes.byref(blocks))
         return rows, prow.value, blocks.value
     L.training_route = training
+
+    def attention(dh, B, H, R, T, empty=False, qoff=0):
+        ns = ctypes.c_int()
+        return ("split", "wide", "tiled")[L.attention(dh, B, H, R, qoff, T, int(empty), ctypes.byref(ns))], ns.value
+    L.attention_route = attention
     return L
 
 
@@ -80,3 +90,44 @@ def test_gpu_shapes_reach_the_32_row_kernel(routes):
     from tests import test_gpu_training_attention_grids as G
     for mask, N, k, dh, BH in G.LARGE + G.HALVES:
         assert routes.training_route(dh, BH, mask, N, k)[0] == 32, (mask, N, k, dh, BH)
+
+
+# (d_head, sequences, heads, rows, capacity, starts empty, kernel), time of the tiled
+# kernel over the one of key splits or of one workgroup per 16 rows
+@pytest.mark.parametrize("dh,B,H,R,T,empty,want", [
+    (64, 1, 12, 32, 1024, False, "split"),    # one sequence, k = 16, 880 keys: 1.61
+    (128, 1, 12, 32, 1024, False, "split"),   # 1.98
+    (32, 1, 12, 34, 1024, False, "split"),    # 1.44
+    (128, 4, 12, 32, 1024, False, "split"),   # 1.22
+    (32, 8, 12, 34, 1024, False, "split"),    # 288 blocks without splits: 1.20
+    (64, 2, 12, 34, 1024, False, "wide"),
+    (64, 16, 12, 34, 1024, False, "tiled"),   # 0.68
+    (128, 8, 12, 32, 1024, False, "tiled"),   # two splits: 0.90
+    (32, 64, 12, 32, 1024, False, "tiled"),   # 0.65
+    (64, 1, 12, 65, 1024, True, "tiled"),     # a prompt of 61: 0.82
+    (64, 1, 12, 65, 128, True, "split"),      # no splits at 128 keys: 1.14
+    (128, 1, 12, 65, 128, True, "split"),     # 1.37
+    (32, 1, 12, 384, 1024, True, "split"),    # 288 blocks: 1.20
+    (64, 4, 12, 96, 1024, True, "split"),     # 288 blocks: 1.14
+    (64, 8, 12, 511, 1024, True, "tiled"),
+    (64, 24, 16, 704, 1024, True, "tiled"),
+    (64, 64, 12, 20, 128, True, "split"),     # fewer than 32 rows
+])
+def test_attention_kernel(routes, dh, B, H, R, T, empty, want):
+    assert routes.attention_route(dh, B, H, R, T, empty)[0] == want
+
+
+def test_attention_of_a_part_of_the_rows_is_never_tiled(routes):
+    """The tiled kernel starts at row 0 of a step: the last layer's noise rows go elsewhere."""
+    for B in (1, 8, 64, 512):
+        for R in (33, 64, 200):
+            assert routes.attention_route(64, B, 12, R, 1024, True, qoff=1)[0] != "tiled"
+
+
+def test_gpu_shapes_reach_their_kernels(routes):
+    from tests import test_gpu_attention_routes as G
+    for kernel, d, H, B, n_ctx, N in G.DECODE:
+        for R in (32, 33):
+            assert routes.attention_route(d // H, B, H, R, n_ctx)[0] == kernel, (kernel, d, H, B, R)
+    for d, H, B, rows in G.PREFILL:
+        assert routes.attention_route(d // H, B, H, rows, 384, True) == ("tiled", 1), (d, H, B, rows)
