@@ -345,7 +345,8 @@ __device__ __forceinline__ void attend(unsigned char* smem, const Item& C, const
   for (int j = 0; j < S - 1; ++j) issue(j, j);
 
   // running max m (log2 units); o = the unnormalised O^T; ls = this lane's part
-  // of the row sum, over the bf16 probabilities that o uses
+  // of the row sum: over the bf16 probabilities that o uses, or, in a model's step
+  // over the cache, over the fp32 ones as in the other kernels of block attention
   float m_run = -INFINITY;
   ls = 0.f;
 #pragma unroll
@@ -446,8 +447,11 @@ __device__ __forceinline__ void attend(unsigned char* smem, const Item& C, const
         const bf16x2_t h = __builtin_convertvector(e, bf16x2_t);
         pf[j][r] = h[0];
         pf[j][r + 1] = h[1];
-        ls = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(s16x2_t, h),
-                                             __builtin_bit_cast(s16x2_t, one2), ls, false);
+        if constexpr (Keys::kPaged)
+          ls += e[0] + e[1];
+        else
+          ls = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(s16x2_t, h),
+                                               __builtin_bit_cast(s16x2_t, one2), ls, false);
       }
     // O^T += V^T P^T, 16 keys a step
     lgkm_wait0();
@@ -474,12 +478,11 @@ __device__ __forceinline__ void attend(unsigned char* smem, const Item& C, const
   ls = __uint_as_float(both[0]) + __uint_as_float(both[1]);
 }
 
-// This lane's normalised output row (d_head DH): the halves exchange 4-value
-// pieces so that each stores 16 bytes.
+// This lane's normalised output row (d_head DH), inv = 1 / its row sum: the halves
+// exchange 4-value pieces so that each stores 16 bytes.
 template <int DH>
 __device__ __forceinline__ void store_row(bf16* orow, bool valid, const f32x16_t (&o)[DH / 32],
-                                          float ls) {
-  const float inv = __builtin_amdgcn_rcpf(ls);
+                                          float inv) {
   const int half = (threadIdx.x & 63) >> 5;
 #pragma unroll
   for (int eg = 0; eg < DH / 32; ++eg)
@@ -560,7 +563,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH
   // O: [B][H][nq][DH], or [B][nq][H][DH] (rows of a residual stream) with o_inter
   const int ob = C.bh / H, oh = C.bh - ob * H;
   store_row<DH>(O + (o_inter ? (((size_t)ob * nq + row) * H + oh) * DH : ((size_t)C.bh * nq + row) * DH),
-                valid, o, ls);
+                valid, o, __builtin_amdgcn_rcpf(ls));
 }
 
 // Attention of a step with many rows per sequence (a prefill) over the paged KV
@@ -608,7 +611,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(DH
   const PagedKeys<DH> keys{kv, kg, __builtin_amdgcn_readfirstlane(g.slot(b)),
                            kg.head_off(layer, 0, h), kg.head_off(layer, 1, h), ctx + g.R};
   attend<DH, S, NW>(smem, C, keys, rs, qf, c2, o, ls);
-  store_row<DH>(O + at, valid, o, ls);
+  store_row<DH>(O + at, valid, o, 1.0f / ls);
 }
 
 // The same mask with 16 query rows per wavefront (64 per workgroup) on 16x16x32
