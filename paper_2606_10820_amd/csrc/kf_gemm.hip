@@ -841,8 +841,10 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
 #pragma unroll
     for (int y = 0; y < TM; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
   // fp32 keeps the odd K slices' sums apart: chains of half the length, whose
-  // rounding is what is left of an fp32 model's error.
-  constexpr bool kTwoSums = sizeof(T) == 4 && !kBig && !IsHead<Ep>::value;
+  // rounding is what is left of an fp32 model's error.  Not in 128 x 128 tiles:
+  // there the second set does not fit 128 registers (QKV 4096 x 2304, K = 768 152
+  // us with one set, 160 with two; 162 with two sets and two wavefronts per SIMD).
+  constexpr bool kTwoSums = sizeof(T) == 4 && BM * BN < 128 * 128 && !IsHead<Ep>::value;
   f32x4 acc1[kTwoSums ? TN : 1][kTwoSums ? TM : 1];
   if constexpr (kTwoSums) {
 #pragma unroll
