@@ -20,6 +20,7 @@
 
 #include "kf_internal.h"
 #include "kf_lds.h"
+#include "kf_route.h"
 
 namespace kf {
 namespace {
@@ -1794,15 +1795,13 @@ hipError_t launch_plain(const GemmA& ga, const T* W, int M, int N, int K, const 
   const int tiles = ((N + BN - 1) / BN) * ((M + BM - 1) / BM);
   constexpr int BK = KCH * 16 / (int)sizeof(T);
   const int nk = K / BK;
-  // A grid of one half to one workgroup per CU, or a smaller one whose K is
-  // too short to split across workgroups, runs two K groups per workgroup
-  // (eight wavefronts, each group half the K steps with its own ring, the
-  // halves summed in LDS) when both rings fit the CU's LDS.
+  // On some grids (two_groups) a workgroup runs two K groups (eight wavefronts,
+  // each group half the K steps with its own ring, the halves summed in LDS)
+  // when both rings fit the CU's LDS.
   // (The tiles of up to 64 x 64 only: the larger ones run on grids of 256
   // workgroups or more.)
   constexpr bool kFit2 = BM * BN <= 64 * 64 && 2 * S * (BM + BN) * KCH * 16 <= 160 * 1024;
-  const bool grid2 = tiles >= kTwoGroupMin ? tiles <= kTwoGroupMax : nk < 24 || sizeof(T) == 4;
-  const int kg = kFit2 && grid2 && nk % 2 == 0 && nk >= 8 ? 2 : 1;
+  const int kg = kFit2 && two_groups(sizeof(T) == 4, tiles, nk) && nk % 2 == 0 && nk >= 8 ? 2 : 1;
   const int nkg = nk / kg;
   int ks = 1;
   // Long-K grids of up to one workgroup per CU split too (in two): at

@@ -1,4 +1,4 @@
-// kf_route.h -- which attention kernel a call runs: rules on its sizes alone.
+// kf_route.h -- which kernel variant a call runs: rules on its sizes alone.
 // Host code without HIP types, so that a host compiler can test the rules.
 #pragma once
 
@@ -97,6 +97,17 @@ inline AttentionRoute attention_route(int dh, int B, int H, int R, int qoff, int
   else if (tiled)
     tiled = base >= (dh == 32 ? 576 : 256);
   return {ns, wide, tiled};
+}
+
+// Plain GEMMs (out-projection, MLP-down, noise encoder): two K groups per workgroup
+// on a grid of `tiles` tiles of at most 64 x 64 with nk K steps each.  Half to one
+// workgroup per CU: two groups.  Fewer: two groups where K is too short to be split
+// across workgroups; in fp32 also at nk = 24, whose split does not pay either
+// (out-projection, K = 768, up to 144 rows: 9.6 -> 8.8 us).  Longer K splits: in
+// fp32 two groups took 1.04 to 1.34 times as long there (K = 1024 1.17, K = 2048
+// 1.21, K = 3072 1.19, K = 4096 1.34 at most; 1 to 64 sequences of 2 to 8 rows).
+inline bool two_groups(bool fp32, int tiles, int nk) {
+  return tiles >= 128 ? tiles <= 256 : nk < 24 || (fp32 && nk == 24);
 }
 
 }  // namespace kf

@@ -1,4 +1,4 @@
-"""The size rules that choose an attention kernel (csrc/kf_route.h), compiled for
+"""The size rules that choose a kernel variant (csrc/kf_route.h), compiled for
 the host: each shape below goes to the kernel that measured faster there, and the
 shapes of the GPU tests reach the kernels that they are written for."""
 import ctypes
@@ -22,6 +22,7 @@ extern "C" int attention(int dh, int B, int H, int R, int qoff, int T, int empty
   *ns = r.ns;
   return r.tiled ? 2 : r.wide ? 1 : 0;
 }
+extern "C" int two_groups(int fp32, int tiles, int nk) { return kf::two_groups(fp32 != 0, tiles, nk); }
 """
 
 
@@ -131,3 +132,17 @@ def test_gpu_shapes_reach_their_kernels(routes):
             assert routes.attention_route(d // H, B, H, R, n_ctx)[0] == kernel, (kernel, d, H, B, R)
     for d, H, B, rows in G.PREFILL:
         assert routes.attention_route(d // H, B, H, rows, 384, True) == ("tiled", 1), (d, H, B, rows)
+
+
+# (fp32, tiles, K steps), time of two K groups over splits of K
+@pytest.mark.parametrize("fp32,tiles,nk,want", [
+    (1, 48, 24, True),     # out-projection at K = 768: 0.92
+    (1, 64, 32, False),    # K = 1024: 1.17
+    (1, 96, 128, False),   # MLP-down at K = 4096: 1.34
+    (1, 72, 96, False),    # K = 3072: 1.19
+    (1, 64, 10, True), (0, 64, 10, True),   # too short to split
+    (0, 96, 48, False), (0, 96, 24, False),
+    (1, 128, 96, True), (0, 256, 48, True), (0, 257, 48, False),
+])
+def test_k_groups_of_small_grids(routes, fp32, tiles, nk, want):
+    assert bool(routes.two_groups(fp32, tiles, nk)) == want
