@@ -1888,12 +1888,9 @@ hipError_t dispatch(const GemmA& ga, const T* W, int Mend, int N, int K, const E
           if (e != hipSuccess) return e;
           return dispatch<T, MODE, NORM>(ga, W, M, N, K, ep, s, ws, big);
         }
+        if (mlp_up_four_waves(cdiv(M, 128) * cdiv(N, 128), K))
+          return launch_tile<T, 128, 128, 2, 2, 2, MODE, NORM>(ga, W, K, Mend, N, K, ep, s, 1, mlo);
       }
-      // Four wavefronts per 128 x 128 tile where K is long enough for the
-      // lighter LDS reads to pay for a longer epilogue (16896 x 3072, K = 1024
-      // 139 -> 132 us; 9000 x 2304, K = 768 46.9 -> 47.8).
-      if (cdiv(M, 128) * cdiv(N, 128) >= kFill && K >= 1024 && K % (2 * KCH * 8) == 0)
-        return launch_tile<T, 128, 128, 2, 2, 2, MODE, NORM>(ga, W, K, Mend, N, K, ep, s, 1, mlo);
     }
     if (cdiv(M, 128) * cdiv(N, 128) >= kFill)
       return launch_tile<T, 128, 128, 2, 4, 2, MODE, NORM>(ga, W, K, Mend, N, K, ep, s, 1, mlo);

@@ -110,4 +110,11 @@ inline bool two_groups(bool fp32, int tiles, int nk) {
   return tiles >= 128 ? tiles <= 256 : nk < 24 || (fp32 && nk == 24);
 }
 
+// MLP-up (16 bits, K columns) in 128 x 128 tiles: four wavefronts where K is long
+// enough for their lighter LDS reads to pay for a longer epilogue (K = 1024, 3500 to
+// 8200 rows: 0.96 to 1.01 of eight wavefronts' time).  Eight below, and always for
+// QKV, whose epilogue, the KV append, is the longer one: K = 1024, 1400 to 19800 rows
+// 1.05 to 1.32 times as long in four (4096 x 3072 37 -> 45 us).
+inline bool mlp_up_four_waves(int tiles, int K) { return tiles >= 256 && K >= 1024 && K % 128 == 0; }
+
 }  // namespace kf

@@ -146,3 +146,14 @@ def test_gpu_shapes_reach_their_kernels(routes):
 ])
 def test_k_groups_of_small_grids(routes, fp32, tiles, nk, want):
     assert bool(routes.two_groups(fp32, tiles, nk)) == want
+
+
+def test_qkv_runs_no_tile_of_four_wavefronts(tmp_path):
+    """The built library holds 128 x 128 tiles of four wavefronts for MLP-up and the heads,
+    none for QKV (K = 1024: up to 1.32 times as long as eight)."""
+    from tests.test_kernel_registers import LIB, READELF, _kernels
+    if not (os.path.exists(LIB) and os.path.exists(READELF)):
+        pytest.skip("needs the built library and llvm-readelf")
+    four = [n for n, _ in _kernels(tmp_path) if "gemm_kernelIDF16bLi128ELi128ELi2ELi2E" in n]
+    assert any("EpBias" in n for n in four) and any("EpHead" in n for n in four)
+    assert [n for n in four if "EpQKV" in n] == []
