@@ -1829,13 +1829,6 @@ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 // Steps of at most this many rows run the skinny kernel (16-bit operands).
 constexpr int kSkinnyRows = 16;
 
-// The time of `tiles` tiles at two workgroups per CU, in fifths of a round: a
-// last round of one workgroup per CU or less takes about three.
-inline int tile_rounds(int tiles) {
-  const int rest = tiles % 512;
-  return tiles / 512 * 5 + (rest == 0 ? 0 : rest <= 256 ? 3 : 5);
-}
-
 // Tile choice: the largest tile that still gives about one workgroup per CU.
 template <typename T, int MODE, bool NORM, class Ep>
 hipError_t dispatch(const GemmA& ga, const T* W, int Mend, int N, int K, const Ep& ep, hipStream_t s,
@@ -1849,17 +1842,11 @@ hipError_t dispatch(const GemmA& ga, const T* W, int Mend, int N, int K, const E
   constexpr int kFill = 256;
   if constexpr (!NORM && MODE == 0) {
     if constexpr (sizeof(T) == 2) {
-      // Two workgroups of four wavefronts per CU; 160 rows where they save a
-      // round (see tile_rounds): residual 11808 x 768, K = 3072 83 -> 61 us and
-      // K = 768 34 -> 27, 16896 x 1024, K = 4096 178 -> 166.  128 rows in four
-      // wavefronts against eight: 16384 x 1024, K = 4096 139 -> 132, 9000 x
-      // 768, K = 3072 52 -> 49.
-      const int t128 = cdiv(M, 128) * cdiv(N, 128), t160 = cdiv(M, 160) * cdiv(N, 128);
-      if (t128 >= kFill && K % (2 * KCH * 8) == 0) {
-        if (6 * tile_rounds(t160) < 5 * tile_rounds(t128))
-          return launch_tile<T, 160, 128, 2, 2, 2, MODE, NORM>(ga, W, K, M, N, K, ep, s);
+      const int rows = plain_tile_rows(cdiv(M, 128) * cdiv(N, 128), cdiv(M, 160) * cdiv(N, 128), K);
+      if (rows == 160)
+        return launch_tile<T, 160, 128, 2, 2, 2, MODE, NORM>(ga, W, K, M, N, K, ep, s);
+      if (rows == 128)
         return launch_tile<T, 128, 128, 2, 2, 2, MODE, NORM>(ga, W, K, M, N, K, ep, s);
-      }
     }
     if (cdiv(M, 128) * cdiv(N, 128) >= kFill)
       return launch_plain<T, 128, 128, 2, 4, 2>(ga, W, M, N, K, ep, s, ws);

@@ -117,4 +117,25 @@ inline bool two_groups(bool fp32, int tiles, int nk) {
 // 1.05 to 1.32 times as long in four (4096 x 3072 37 -> 45 us).
 inline bool mlp_up_four_waves(int tiles, int K) { return tiles >= 256 && K >= 1024 && K % 128 == 0; }
 
+// The time of `tiles` tiles at two workgroups per CU, in fifths of a round: a
+// last round of one workgroup per CU or less takes about three.
+inline int tile_rounds(int tiles) {
+  const int rest = tiles % 512;
+  return tiles / 512 * 5 + (rest == 0 ? 0 : rest <= 256 ? 3 : 5);
+}
+
+// Plain GEMMs (16 bits, K columns) of 256 tiles of 128 x 128 and more, t160 of 160 x
+// 128: rows of the four-wavefront tile to run, two workgroups per CU, or 0 for 128
+// rows in eight wavefronts.  160 where they save more rounds than their tiles are
+// larger: 0.66 to 0.98 of eight wavefronts' time (residual 11808 x 768, K = 3072 83 ->
+// 61 us; K = 768 34 -> 27; 16896 x 1024, K = 4096 178 -> 166); at 8 fifths against
+// 10, an equal sum, they took 0 to 9 % longer than 128.  128 rows in four wavefronts:
+// 0.92 to 1.02 of eight on one round (K = 4096 up to 1.08), and at K = 2048 and more
+// beyond; at K = 768 and 1024 on more than one round 1.00 to 1.06.
+inline int plain_tile_rows(int t128, int t160, int K) {
+  if (t128 < 256 || K % 128 != 0) return 0;
+  if (5 * tile_rounds(t160) < 4 * tile_rounds(t128)) return 160;
+  return t128 <= 512 || K > 1024 ? 128 : 0;
+}
+
 }  // namespace kf

@@ -22,6 +22,7 @@ extern "C" int attention(int dh, int B, int H, int R, int qoff, int T, int empty
   *ns = r.ns;
   return r.tiled ? 2 : r.wide ? 1 : 0;
 }
+extern "C" int plain_rows(int t128, int t160, int K) { return kf::plain_tile_rows(t128, t160, K); }
 extern "C" int two_groups(int fp32, int tiles, int nk) { return kf::two_groups(fp32 != 0, tiles, nk); }
 """
 
@@ -157,3 +158,20 @@ def test_qkv_runs_no_tile_of_four_wavefronts(tmp_path):
     four = [n for n, _ in _kernels(tmp_path) if "gemm_kernelIDF16bLi128ELi128ELi2ELi2E" in n]
     assert any("EpBias" in n for n in four) and any("EpHead" in n for n in four)
     assert [n for n in four if "EpQKV" in n] == []
+
+
+# (M, N, K, rows of the four-wavefront tile or 0), its time over eight wavefronts of 128 rows
+@pytest.mark.parametrize("M,N,K,want", [
+    (11808, 768, 3072, 160),    # 0.73
+    (16896, 1024, 4096, 160),   # 0.84
+    (8192, 768, 3072, 128),     # 0.94
+    (12288, 1024, 4096, 128),   # 0.96
+    (19200, 768, 768, 0),       # 900 tiles of 128 rows, 720 of 160: 1.04 and more in either
+    (18432, 768, 3072, 128),    # 160 rows against 128: 1.07
+    (13312, 1024, 1024, 0),     # 160 rows: 1.04
+    (4000, 768, 3072, 0),       # fewer than 256 tiles
+    (8192, 768, 832, 0),        # an odd number of K steps
+])
+def test_plain_tiles(routes, M, N, K, want):
+    tiles = lambda rows: -(-M // rows) * -(-N // 128)  # noqa: E731
+    assert routes.plain_rows(tiles(128), tiles(160), K) == want
