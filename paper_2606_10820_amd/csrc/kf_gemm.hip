@@ -319,13 +319,10 @@ struct EpQKV {
   // < M) of value column n.  Rows that are consecutive slots of one sequence
   // within one value block are one contiguous run, and consecutive lanes hold
   // consecutive value rows, whose runs are adjacent.
-  // On a small grid (M <= 512, bound by latency) they go out like key rows unless
-  // a sequence's rows can fall into whole blocks: by column a lane computes up to
-  // ten slots one after another there, by row one.  (Asking the committed length
-  // whether they do costs a load: one sequence, 11.00 -> 11.08 ms a generate.)
+  // On small grids (bound by latency) they go out like key rows: by column a lane
+  // computes up to ten slots one after another, by row one (value_columns).
   __device__ inline bool column_tile(int n0, int M) const {
-    if (n0 < 2 * kg.H * kg.dh) return false;
-    return M > 512 || (sizeof(T) == 2 && g.R % 4 == 0);
+    return n0 >= 2 * kg.H * kg.dh && value_columns(sizeof(T) == 4, M, g.R);
   }
   //
   // Every index into v is a compile-time constant (a run-time index would put

@@ -1,5 +1,5 @@
 // kf_route.h -- which kernel variant a call runs: rules on its sizes alone.
-// Host code without HIP types, so that a host compiler can test the rules.
+// Without HIP types, so that a host compiler can test the rules.
 #pragma once
 
 namespace kf {
@@ -136,6 +136,18 @@ inline int plain_tile_rows(int t128, int t160, int K) {
   if (t128 < 256 || K % 128 != 0) return 0;
   if (5 * tile_rounds(t160) < 4 * tile_rounds(t128)) return 160;
   return t128 <= 512 || K > 1024 ? 128 : 0;
+}
+
+// QKV value tiles of M rows, R a sequence: by column (a lane stores runs of 4 slots)
+// or by row.  By column the time depends on whether the rows fall into whole 4-slot
+// blocks, which the committed length decides as well as R, and the host rule does not
+// know it (asking on the device costs every launch a load: one sequence, 11.00 ->
+// 11.08 ms a generate).  QKV at K = 768, k = 4, us by row against by column, contexts
+// of 16 | 17:  M = 48 6.8, 7.1 | 7.1, 8.8;  192 8.0, 8.0 | 8.8, 10.1;  256 8.9, 8.9 |
+// 9.8, 11.2;  384 9.3, 9.0 | 10.4, 11.3;  512 11.6, 11.0 | 12.7, 15.2 (K = 1024 at 512
+// 13.5, 12.0 | 14.8, 16.1).  fp32: 512 28.4, 27.6 | 29.7, 32.4.
+constexpr bool value_columns(bool fp32, int M, int R) {
+  return M > 512 || (!fp32 && M > 256 && R % 4 == 0);
 }
 
 }  // namespace kf
