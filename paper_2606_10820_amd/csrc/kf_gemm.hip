@@ -904,7 +904,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
   // partials are loaded before the operand loads are issued (so waiting for
   // them does not wait for the operands) and reduced by the TPR consecutive
   // lanes that share a row.
-  static_assert(!NORM || NT >= BM, "at least one thread per row for the statistics");
+  static_assert(!NORM || NT % BM == 0, "whole threads per row for the statistics");
   constexpr int TPR = NORM ? NT / BM : 1;
   // float4 loads (two partials each) per lane, unrolled: whole rows up to
   // K = 1024; wider rows finish in a loop.
@@ -920,7 +920,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
   // are never consumed (the buffer range returns zeros past its end), and it
   // has landed before the first barrier.
   if constexpr (NORM) {
-    const int r = tid / TPR, gr = m0 + r < M ? m0 + r : M - 1;  // r < BM, or a row not stored
+    const int r = tid / TPR, gr = m0 + r < M ? m0 + r : M - 1;
     prow = reinterpret_cast<const float4*>(ga.lnst + (size_t)map_row<MODE>(gr, ga.g) * (K / 16));
 #pragma unroll
     for (int j = 0; j < PMAX; ++j) {
@@ -977,8 +977,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG)
     }
 #pragma unroll
     for (int off = 1; off < TPR; off <<= 1) b += __shfl_xor(b, off, 64);
-    if (tid % TPR == 0 && (NT % BM == 0 || tid / TPR < BM))
-      sStat[tid / TPR] = make_float2(mu, 1.0f / sqrtf(b / (float)K + 1e-5f));
+    if (tid % TPR == 0) sStat[tid / TPR] = make_float2(mu, 1.0f / sqrtf(b / (float)K + 1e-5f));
   }
   if (nk > S - 1) vm_wait<(S - 1) * PER>();
   else vm_wait<0>();
