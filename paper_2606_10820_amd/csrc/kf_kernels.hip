@@ -485,7 +485,12 @@ __global__ void __launch_bounds__(64)
   const bool fall = cross == 0;
   const int L = !fall ? __ffsll((unsigned long long)cross) - 1
                       : (pos ? 63 - __clzll((unsigned long long)pos) : 0);
-  float run = incl - ls, before = run;  // mass before this lane's next tile; before the pick
+  // mass before this lane's next tile; before the pick.  Prefixes of the elements
+  // before, here and below, not differences: a mass lost in a sum of its own lane
+  // would be skipped at u = 0.
+  float run = __shfl_up(incl, 1, 64);
+  if (lane == 0) run = 0.f;
+  float before = run;
   int pick = -1, last = lo;
   float last_run = run;
   auto step = [&](int t, float wt) {
@@ -517,7 +522,7 @@ __global__ void __launch_bounds__(64)
   const float p0 = j < V ? expf(l[j] - mt) * sc : 0.f;
   const float p1 = j + 1 < V ? expf(l[j + 1] - mt) * sc : 0.f;
   const float end = before + wave_scan(p0 + p1, lane);  // prefix through column j + 1
-  const float mid = end - p1;
+  const float prev = __shfl_up(end, 1, 64), mid = (lane == 0 ? before : prev) + p0;
   const uint64_t hit = fall ? 0 : __ballot(end > thr && p0 + p1 > 0.f);
   int col;
   if (hit) {
