@@ -309,22 +309,17 @@ def _short(name: str) -> str:
 
 
 KERNEL_SOURCES = os.path.join(ROOT, "paper_2606_10820_amd", "csrc")
-# the training-mask attention source holds no kernel of the decode step
-DECODE_EXCLUDED = ("kf_blockattn.hip",)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_lm1b_b64_k4.json")
 
 
 def kernel_source_hash() -> str:
-    """sha256 over the sources of the decode step's kernels and their launch
-    code, with comments and whitespace removed: counter figures taken from
-    different code are not reported (an edit of a comment does not change the
-    kernels)."""
+    """sha256 over the sources of the kernels and their launch code, with
+    comments and whitespace removed: counter figures taken from different code
+    are not reported (an edit of a comment does not change the kernels)."""
     import hashlib
     import re
     h = hashlib.sha256()
     for fn in sorted(os.listdir(KERNEL_SOURCES)):
-        if fn in DECODE_EXCLUDED:
-            continue
         with open(os.path.join(KERNEL_SOURCES, fn), encoding="utf-8") as f:
             src = f.read()
         src = re.sub(r"/\*.*?\*/", " ", src, flags=re.S)
@@ -342,13 +337,14 @@ def kernel_class(name: str, state: dict):
         return "embed"
     if "noise_sinusoid" in name or "EpNoiseOut" in name:
         return "noise"
-    if "attention_mfma_kernel" in name or "attention_combine_kernel" in name:
+    if any(k in name for k in ("attention_mfma_kernel", "attention_f32_kernel", "attention_combine_kernel",
+                               "prefill_attention_kernel", "training_attention")):
         return "attn"
     if "EpQKV" in name:
         return "qkv"
     if "EpHead" in name:
         return "head"
-    if any(k in name for k in ("argmax_select_kernel", "icdf_select_kernel", "commit_kernel")):
+    if any(k in name for k in ("argmax_select_kernel", "icdf_select_kernel")):
         return "select"
     if "EpPartial" in name:
         return "pending"

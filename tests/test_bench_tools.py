@@ -5,6 +5,9 @@ reduction that follows it, an attention combine with its attention, and a
 part with no reduction after it (the noise encoder's fp32 output GEMM) as
 noise."""
 import csv
+import os
+import re
+import shutil
 
 import bench
 
@@ -66,3 +69,31 @@ def test_short_names_show_k_groups():
     one = GEMM + "Lb1ENS0_6EpBiasIDF16bEELi1EEEvNS0_5GemmAEPKT_iiiiT7_i"
     assert bench._short(two) == "gemm 32x64 2g EpResidual bf16"
     assert bench._short(one) == "gemm 32x64 EpBias bf16"
+
+
+def test_every_attention_kernel_of_the_sources_is_classified():
+    """A kernel with attention in its name belongs to the attn class: one that is not
+    named in kernel_class would drop out of the class times and the traffic tables."""
+    names = set()
+    for fn in os.listdir(bench.KERNEL_SOURCES):
+        with open(os.path.join(bench.KERNEL_SOURCES, fn), encoding="utf-8") as f:
+            names |= set(re.findall(r"\b(\w*attention\w*_kernel)\(", f.read()))
+    assert {"attention_mfma_kernel", "attention_f32_kernel", "prefill_attention_kernel",
+            "training_attention_kernel", "training_attention16_kernel"} <= names
+    for n in names:
+        assert bench.kernel_class(_NS + f"{len(n)}{n}ILi64EEEvv", {}) == "attn", n
+
+
+def test_source_hash_covers_every_kernel_source(tmp_path, monkeypatch):
+    """An edit of any source changes the hash (kf_generate runs kernels of each), one of a comment does not."""
+    for fn in sorted(os.listdir(bench.KERNEL_SOURCES)):
+        shutil.copy(os.path.join(bench.KERNEL_SOURCES, fn), tmp_path / fn)
+    monkeypatch.setattr(bench, "KERNEL_SOURCES", str(tmp_path))
+    before = bench.kernel_source_hash()
+    for f in sorted(tmp_path.iterdir()):
+        text = f.read_text()
+        f.write_text(text + "\n// a comment\n")
+        assert bench.kernel_source_hash() == before, f.name
+        f.write_text(text + "\nint added;\n")
+        assert bench.kernel_source_hash() != before, f.name
+        f.write_text(text)
