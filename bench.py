@@ -333,7 +333,7 @@ def kernel_class(name: str, state: dict):
     """Kernel class of one dispatch, from its name and the launch order of a
     step: out-proj and MLP-down share one GEMM instantiation and alternate;
     a split-K part belongs to the reduction that follows it."""
-    if "embed_real_kernel" in name:
+    if "embed_real_kernel" in name or "embed_group_kernel" in name:
         return "embed"
     if "noise_sinusoid" in name or "EpNoiseOut" in name:
         return "noise"
@@ -344,7 +344,7 @@ def kernel_class(name: str, state: dict):
         return "qkv"
     if "EpHead" in name:
         return "head"
-    if any(k in name for k in ("argmax_select_kernel", "icdf_select_kernel")):
+    if any(k in name for k in ("argmax_select_kernel", "icdf_select_kernel", "teacher_select_kernel")):
         return "select"
     if "EpPartial" in name:
         return "pending"
