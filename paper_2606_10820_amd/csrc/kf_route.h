@@ -14,14 +14,22 @@ struct TrainingRoute {
 
 // 32 rows share each tile's transfer among twice the rows; 16 give twice the
 // workgroups, half the serial work of each and less padding of the last block.
-// Times of the 32-row kernel over the 16-row one, both masks, 8 to 4096 heads, N
-// from 1 to 1000, k = 1, 2, 4, 8, against the number of 128-row workgroups:
-//   d_head 128  384 and more 0.81 on average, 1.04 at most; fewer 1.05 to 1.35
-//   d_head 64   3072 and more 0.91, 1.05 at most; 1024 and more at N of 80 to 255
-//               likewise (self-forcing rollouts); else up to 1.35
-//   d_head 32   1024 and more 0.84, 1.07 at most; fewer up to 1.13
-// where a head's last workgroup is nearly whole: the rows padded to 128 a block may
-// exceed those padded to 64 by 1/24 (d_head 128: 1/5).  Beyond that 1.05 to 1.26.
+// Times of the 32-row kernel over the 16-row one (3529 shapes: both masks, 8 to 4096
+// heads, N from 1 to 1000, k = 1, 2, 4, 8), by the number of 128-row workgroups
+// ("grid"), blocks per part, and rows in the last one ("last"):
+//   d_head 128  grid of 384 and more 0.82 on average; from 288 on with three blocks
+//               and last > 64 0.9.  One block of 64 rows and less 1.04 to 1.22, two
+//               blocks with last <= 32 from grid 1024 on up to 1.10, smaller grids
+//               1.05 to 1.35
+//   d_head 64   0.90 where last > 64 and the grid is of 512 and more and fills whole
+//               rounds of 768 (three workgroups per CU) by 85 % (M_S: N under 256,
+//               beyond it up to 1.06), or is of 3072, or the head is one block, or two
+//               with last <= 96, or N is of 80 to 255 on a grid of 1024 (self-forcing
+//               rollouts); on 3072 also where the padding of the last block is under
+//               1/24 of the rows.  Else up to 1.40
+//   d_head 32   0.85 where last > 64 on 768 and more (one block: 512), last >= 32 in
+//               six blocks and more on 3072, or little padding on 1024.  Else up to 1.40
+// The most among the shapes that the rule gives to the 32-row kernel is 1.07.
 //
 // M_D has two halves of N k rows.  A block across their border would walk nearly
 // all Future-1 keys (the last groups see the last ones, the first groups the
@@ -32,12 +40,21 @@ inline TrainingRoute training_route(int dh, long long BH, bool two_parts, long l
   const bool cut = two_parts && N * k >= 512;
   const long long prow = cut ? nq / 2 : nq;
   const long long b32 = (prow + 127) / 128 * (cut ? 2 : 1), b16 = (nq + 63) / 64;
-  const long long grid = BH * b32;
-  const bool whole = 48 * b32 <= 25 * b16;
+  const long long grid = BH * b32, blocks = (prow + 127) / 128, last = prow - 128 * (blocks - 1);
+  const bool full = last > 64, whole = 48 * b32 <= 25 * b16;
   bool r32;
-  if (dh == 128) r32 = grid >= 384 && 10 * b32 <= 6 * b16;
-  else if (dh == 64) r32 = (whole && grid >= 3072) || (2 * b32 == b16 && grid >= 1024 && N >= 80 && N < 256);
-  else r32 = whole && grid >= 1024;
+  if (dh == 128)
+    r32 = (grid >= 384 && prow > 64 && !(blocks == 2 && last <= 32 && grid >= 1024)) ||
+          (grid >= 288 && full && blocks >= 3);
+  else if (dh == 64)
+    r32 = (whole && grid >= 3072) ||
+          (full && grid >= 512 &&
+           (grid >= 3072 || blocks == 1 ||
+            ((two_parts || N < 256) && 20 * grid >= 17 * 768 * ((grid + 767) / 768)) ||
+            (blocks == 2 && last <= 96) || (N >= 80 && N < 256 && grid >= 1024)));
+  else
+    r32 = (whole && grid >= 1024) || (full && grid >= (blocks == 1 ? 512 : 768)) ||
+          (blocks >= 6 && last >= 32 && grid >= 3072);
   return {r32, (int)prow, (int)b32};
 }
 

@@ -13,11 +13,12 @@ from tests.test_gpu_training_attention import KIND, _bd, _check, _run
 pytestmark = pytest.mark.gpu
 np = pytest.importorskip("numpy")
 
-# (mask, N, k, d_head, heads): rows N (1 + k) of 66, 96, 128, 200, 255, 256, 640 under M_S
+# (mask, N, k, d_head, heads): rows N (1 + k) of 66 to 800 under M_S
 LARGE = [(0, 33, 1, 128, 384), (0, 32, 2, 128, 384), (0, 32, 3, 128, 384), (0, 100, 1, 128, 256),
          (0, 127, 1, 64, 512), (0, 85, 2, 64, 512), (0, 128, 1, 64, 512), (0, 128, 4, 64, 256),
          (0, 127, 1, 32, 512), (0, 160, 3, 32, 256),
-         (0, 129, 1, 128, 200), (1, 64, 1, 128, 384), (1, 16, 4, 128, 384)]
+         (0, 129, 1, 128, 200), (0, 43, 2, 128, 200), (0, 32, 4, 128, 200), (0, 160, 4, 32, 512),
+         (1, 64, 1, 128, 384), (1, 16, 4, 128, 384)]
 # M_D halves of N k rows: a workgroup and a wavefront across the border (25, 50, 100, 492,
 # 495, 511: blocks cut from row 0 on), each half by itself (512, 513, 535, 600, 1250)
 HALVES = [(1, 25, 2, 128, 384), (1, 50, 1, 128, 400), (1, 100, 1, 128, 256), (1, 100, 1, 64, 512),

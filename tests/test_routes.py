@@ -57,6 +57,13 @@ def routes(tmp_path_factory):
     (64, 384, 0, 123, 2, 32),    # self-forcing rollout, round 1: 0.94
     (64, 384, 1, 123, 2, 32),    # and round 2: 0.86
     (64, 1024, 1, 16, 1, 16),    # a quarter of a workgroup's rows: 1.34
+    (64, 2048, 0, 8, 8, 32),     # one block of 72 rows: 0.76
+    (64, 128, 0, 1000, 1, 16),   # 2048 workgroups of long rows: 1.06
+    (64, 128, 1, 1000, 1, 32),   # the same under M_D: 0.81
+    (64, 384, 0, 100, 1, 32),    # 200 rows, one round: 0.83
+    (64, 512, 1, 64, 2, 16),     # 256 rows, a round and a third: 1.08
+    (64, 128, 0, 160, 1, 16),    # 384 workgroups: 1.11
+    (64, 1024, 0, 86, 4, 16),    # last block of 46 rows: 1.19
     (64, 512, 0, 16, 8, 16),     # 144 rows, the second workgroup nearly empty: 1.20
     (64, 512, 0, 86, 4, 16),     # 430 rows: 1.17
     (64, 256, 1, 100, 4, 16),    # 800 rows: 1.18
@@ -67,6 +74,10 @@ def routes(tmp_path_factory):
     (128, 512, 0, 215, 4, 32),   # 0.79
     (128, 384, 0, 16, 2, 16),    # 48 rows: 1.14
     (128, 4096, 0, 32, 4, 16),   # 160 rows: 1.10
+    (128, 256, 1, 86, 1, 32),    # 172 rows: 0.80
+    (128, 96, 0, 123, 2, 32),    # 288 workgroups, last block of 113 rows: 0.86
+    (32, 96, 1, 250, 2, 32),     # 0.83
+    (32, 1024, 0, 160, 4, 32),   # last block of 32 rows among seven: 0.85
     (32, 32, 1, 1000, 1, 16),    # 512 workgroups: 16 rows as before
     (32, 1024, 0, 300, 2, 16),   # 900 rows: 1.13
     (32, 512, 0, 250, 4, 32),    # 0.80
