@@ -162,9 +162,10 @@ inline int plain_tile_rows(int t128, int t160, int K) {
 // 11.08 ms a generate).  QKV at K = 768, k = 4, us by row against by column, contexts
 // of 16 | 17:  M = 48 6.8, 7.1 | 7.1, 8.8;  192 8.0, 8.0 | 8.8, 10.1;  256 8.9, 8.9 |
 // 9.8, 11.2;  384 9.3, 9.0 | 10.4, 11.3;  512 11.6, 11.0 | 12.7, 15.2 (K = 1024 at 512
-// 13.5, 12.0 | 14.8, 16.1).  fp32: 512 28.4, 27.6 | 29.7, 32.4.
+// 13.5, 12.0 | 14.8, 16.1); through a page table 192 8.8, 8.8 | 9.5, 11.7;  256 9.7, 9.3
+// | 10.5, 12.6.  fp32: 512 28.4, 27.6 | 29.7, 32.4.
 constexpr bool value_columns(bool fp32, int M, int R) {
-  return M > 512 || (!fp32 && M > 256 && R % 4 == 0);
+  return M > 512 || (!fp32 && M > 224 && R % 4 == 0);
 }
 
 }  // namespace kf
