@@ -90,7 +90,7 @@ def test_training_attention_parity(case):
     _check(got, ref, f"{KIND[mask]} N={N} k={k} dh={dh}")
 
 
-# row counts on both sides of the 128-row workgroup and the 32-row wavefront
+# row counts on both sides of the 64- and 128-row workgroups and their wavefronts'
 # edges: N (1 + k) = 127, 128, 129, 160, 161 (single), 2 N k likewise even
 EDGES = [(0, 1, 2, 127, 1, 64), (0, 2, 1, 43, 2, 64), (0, 1, 2, 32, 3, 128), (0, 1, 1, 32, 4, 32),
          (0, 1, 2, 23, 6, 64), (1, 1, 2, 64, 1, 64), (1, 1, 2, 65, 1, 128), (1, 2, 1, 21, 3, 32),
